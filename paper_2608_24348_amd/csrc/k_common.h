@@ -103,12 +103,69 @@ template <> __device__ __forceinline__ __half to<__half, double>(double v) { ret
 template <> __device__ __forceinline__ __hip_bfloat16 to<__hip_bfloat16, float>(float v) { return __float2bfloat16(v); }
 template <> __device__ __forceinline__ __hip_bfloat16 to<__hip_bfloat16, double>(double v) { return __float2bfloat16(d2f_round_odd(v)); }
 
-// wavefront sum (64 lanes), fixed butterfly order -> deterministic
+// wavefront sum (64 lanes) in every lane: lanes 32, 16, 8, 4, 2, 1 apart are
+// added in that fixed order -> deterministic.  The exchanges are register
+// swaps of half waves and rows and DPP rotations within a row (after the step
+// at distance d the value repeats with period d, so a rotation by d/2 meets the
+// lane d/2 apart): no step waits for LDS, where a shuffle takes a round trip.
+typedef unsigned u2x __attribute__((ext_vector_type(2)));
+// HALF: a[l] + a[l ^ 32] in lanes < 32 and b[l] + b[l ^ 32] in the others;
+// else the same with lanes 16 apart in even and odd rows
+template <bool HALF> __device__ __forceinline__ u2x lane_swap(unsigned a, unsigned b)
+{
+    if constexpr (HALF) return __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    else return __builtin_amdgcn_permlane16_swap(a, b, false, false);
+}
+template <bool HALF> __device__ __forceinline__ float swap_add(float a, float b)
+{
+    const u2x v = lane_swap<HALF>(__float_as_uint(a), __float_as_uint(b));
+    return __uint_as_float(v.x) + __uint_as_float(v.y);
+}
+template <bool HALF> __device__ __forceinline__ double swap_add(double a, double b)
+{
+    const u2x lo = lane_swap<HALF>((unsigned)__double2loint(a), (unsigned)__double2loint(b));
+    const u2x hi = lane_swap<HALF>((unsigned)__double2hiint(a), (unsigned)__double2hiint(b));
+    return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+}
+// v rotated by N lanes within each row of 16
+template <int N> __device__ __forceinline__ float row_ror(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+}
+template <int N> __device__ __forceinline__ double row_ror(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+template <typename A> __device__ __forceinline__ A row_sum(A v)
+{
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    v += row_ror<1>(v);
+    return v;
+}
 template <typename A> __device__ __forceinline__ A wave_sum(A v)
 {
+    v = swap_add<true>(v, v);
+    v = swap_add<false>(v, v);
+    return row_sum(v);
+}
+// The wave sums of v[0..nv) (nv uniform, rounded up to four), each with the
+// bits of wave_sum, into out[0..]: four values share the exchanges, one to a
+// row after the two swaps (a third of the operations of four wave sums).
+template <int NV> __device__ __forceinline__ void wave_sums(const double (&v)[NV], int nv, double* out)
+{
+    static_assert(NV % 4 == 0, "groups of four");
+    const int lane = threadIdx.x & 63, row = lane >> 4;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int i = 0; i < NV; i += 4)
+        if (i < nv) {
+            const double s = row_sum(swap_add<false>(swap_add<true>(v[i], v[i + 1]), swap_add<true>(v[i + 2], v[i + 3])));
+            // rows hold v[i], v[i+2], v[i+1], v[i+3]
+            if ((lane & 15) == 0) out[i + (row >> 1) + 2 * (row & 1)] = s;
+        }
 }
 template <typename A> __device__ __forceinline__ A wave_max(A v)
 {

@@ -12,40 +12,57 @@ namespace semk {
 
 // ------------------------------------------------------------------ finalise kernels
 // fixed-order sums of the partials of NS slots (valid in thread 0): for each
-// slot, thread t adds partials t, t+bd, t+2bd, ... in that order, then the
+// slot, thread t < 256 adds partials t, t+256, t+512, ... in that order, then the
 // per-thread sums are added in a fixed tree.  The slots are read together,
 // eight loads of each in flight, so a finaliser waits for one round of loads
-// where it waited for NS.  red must hold (blockDim.x / 64) * NS values.
+// where it waited for NS.  red must hold 4 * NS values.
 template <int NS>
 static __device__ void slot_sums(const ReqDesc* R, const int (&slot)[NS], double (&out)[NS], double* red)
 {
-    constexpr int U = 8;
-    const SEM_GLOBAL double* p[NS];
-    int cnt[NS], most = 0;
+    constexpr int U = 8, bd = 256;
+    const int t = threadIdx.x;
     double s[NS];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        p[k] = gp(R->part) + (long long)slot[k] * R->pstride;
-        cnt[k] = gp(R->I)[I_PCNT + slot[k]];
-        most = max(most, cnt[k]);
-        s[k] = 0.0;
+    for (int k = 0; k < NS; ++k) s[k] = 0.0;
+    if (t < bd) {
+        const SEM_GLOBAL double* p[NS];
+        int cnt[NS], most = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            p[k] = gp(R->part) + (long long)slot[k] * R->pstride;
+            cnt[k] = gp(R->I)[I_PCNT + slot[k]];
+            most = max(most, cnt[k]);
+        }
+        for (int q = t; q < most; q += U * bd) {
+            double a[NS][U];
+#pragma unroll
+            for (int k = 0; k < NS; ++k)
+#pragma unroll
+                for (int u = 0; u < U; ++u) a[k][u] = q + u * bd < cnt[k] ? p[k][q + u * bd] : 0.0;
+#pragma unroll
+            for (int k = 0; k < NS; ++k)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (q + u * bd < cnt[k]) s[k] += a[k][u];
+        }
     }
-    const int bd = blockDim.x;
-    for (int q = threadIdx.x; q < most; q += U * bd) {
-        double a[NS][U];
 #pragma unroll
-        for (int k = 0; k < NS; ++k)
+    for (int k = 0; k < NS; ++k) s[k] = wave_sum(s[k]);
+    __syncthreads();
+    if (t < bd && (t & 63) == 0) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) a[k][u] = q + u * bd < cnt[k] ? p[k][q + u * bd] : 0.0;
-#pragma unroll
-        for (int k = 0; k < NS; ++k)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (q + u * bd < cnt[k]) s[k] += a[k][u];
+        for (int k = 0; k < NS; ++k) red[(t >> 6) * NS + k] = s[k];
     }
-    block_sum<double, NS>(s, red);
+    __syncthreads();
+    if (t == 0) {
 #pragma unroll
-    for (int k = 0; k < NS; ++k) out[k] = s[k];
+        for (int k = 0; k < NS; ++k) {
+            double v = 0.0;
+            for (int w = 0; w < bd / 64; ++w) v += red[w * NS + k];
+            out[k] = v;
+        }
+    }
+    __syncthreads();
 }
 static __device__ double slot_sum(const ReqDesc* R, int slot, double* red)
 {
@@ -71,48 +88,71 @@ static __device__ double slot_max(const ReqDesc* R, int slot, double* red)
     return m;
 }
 
-// fixed-order sums of nslots (<= 32) consecutive slots at once: 8 groups of
-// 32 threads (the first 256 threads), thread (g, s) adds partials g, g+8, ...
-// of slot s in that order (eight loads in flight); the 8 group sums are then
-// added in group order.  out must hold nslots values.
-static __device__ void multi_slot_sum(const ReqDesc* R, int slot0, int nslots, double* out, double* scratch)
+// fixed-order sums of nslots (<= 32) consecutive slots at once: partials g,
+// g+8, g+16, ... of a slot are added in that order for g = 0..7, then the 8
+// group sums in group order.  A wave to a slot: it reads 256 partials coalesced
+// into LDS (the next 256 in flight meanwhile) and its lanes 0..7 walk the eight
+// chains there.  With a slot to a thread, eight scattered loads in flight, the
+// 1142 partials of a 20^3, N = 9 Arnoldi step took 12 us.  stage must hold 256
+// values per wave, out nslots.
+static __device__ void multi_slot_sum(const ReqDesc* R, int slot0, int nslots, double* out, double* stage)
 {
-    const int t = threadIdx.x, sl = t & 31, g = t >> 5;
-    double acc = 0.0;
-    if (t < 256 && sl < nslots) {
-        const SEM_GLOBAL double* p = gp(R->part) + (long long)(slot0 + sl) * R->pstride;
-        const int cnt = gp(R->I)[I_PCNT + slot0 + sl];
-        int q = g;
-        for (; q + 56 < cnt; q += 64) {
-            double a[8];
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    double* st = stage + (threadIdx.x >> 6) * 256;
+    for (int k = threadIdx.x >> 6; k < nslots; k += nw) {
+        const SEM_GLOBAL double* p = gp(R->part) + (long long)(slot0 + k) * R->pstride;
+        const int cnt = gp(R->I)[I_PCNT + slot0 + k];
+        double a[4];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) a[k] = p[q + 8 * k];
+        for (int u = 0; u < 4; ++u) a[u] = lane + 64 * u < cnt ? p[lane + 64 * u] : 0.0;
+        double acc = 0.0;
+        for (int q0 = 0; q0 < cnt; q0 += 256) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc += a[k];
+            for (int u = 0; u < 4; ++u) st[lane + 64 * u] = a[u];
+            const int q1 = q0 + 256 + lane;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[u] = q1 + 64 * u < cnt ? p[q1 + 64 * u] : 0.0;
+            lds_handoff<true>();
+            if (lane < 8) {
+                const int n = min(256, cnt - q0);
+                int q = lane;
+                for (; q + 56 < n; q += 64) {
+                    double b[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) b[u] = st[q + 8 * u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc += b[u];
+                }
+                for (; q < n; q += 8) acc += st[q];
+            }
+            lds_handoff<true>();
         }
-        for (; q < cnt; q += 8) acc += p[q];
-    }
-    if (t < 256) scratch[t] = acc;
-    __syncthreads();
-    if (t < nslots) {
-        double v = 0.0;
-        for (int k = 0; k < 8; ++k) v += scratch[k * 32 + t];
-        out[t] = v;
+        if (lane < 8) st[lane] = acc;
+        lds_handoff<true>();
+        if (lane == 0) {
+            double v = 0.0;
+            for (int g = 0; g < 8; ++g) v += st[g];
+            out[k] = v;
+        }
+        lds_handoff<true>();
     }
     __syncthreads();
 }
 
 static __device__ __forceinline__ bool finite(double v) { return isfinite(v); }
 
-// The scalar logic of one request, run by one workgroup of 256 threads (the
-// slot sums use every thread and red holds 4 waves x 8 slots; the multi-slot
-// sum uses the first 256).  ri is the request's position in its batch (host
-// arrays).
+// The scalar logic of one request, run by one workgroup of SEM_FIN_THREADS (red
+// holds up to six slots of four waves).  Vectors of the small GMRES
+// system are read by all threads at once into LDS: a thread that walks them in
+// global memory waits about 1 us for each dependent element.  ri is the
+// request's position in its batch (host arrays).
 static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a)
 {
     __shared__ double red[32];
     __shared__ double sums[SEM_MAXM + 2];
-    __shared__ double scratch[256];
+    __shared__ double stage[SEM_FIN_THREADS / 64 * 256];  // the partial sums' staging, or the small GMRES system
+    __shared__ double shc[SEM_MAXM + 1], shs[SEM_MAXM + 1];
+    __shared__ int jsolve;
     SEM_GLOBAL double* S = gp(R->S);
     SEM_GLOBAL int* I = gp(R->I);
     const int t = threadIdx.x;
@@ -185,7 +225,7 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
     case FIN_GM_H2: {
         if (!I[I_GARN]) break;
         const int J = I[I_GJ];
-        multi_slot_sum(R, R_GM, J + 1, sums, scratch);
+        multi_slot_sum(R, R_GM, J + 1, sums, stage);
         // dots with the stored vectors, scaled to the normalised basis
         if (t <= J) S[(a.op == FIN_GM_H1 ? S_GHC : S_GH2) + t] = sums[t] * S[S_GVS + t];
         if (a.op == FIN_GM_H1) {
@@ -197,41 +237,37 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
     }
     case FIN_GM_COL: {
         if (!I[I_GARN]) break;
-        double hn2 = slot_sum(R, R_GN, red);
+        const int m = I[I_GM];
+        const int J = I[I_GJ];
+        SEM_GLOBAL double* H = S + S_GH;
+        if (t <= J) sums[t] = S[S_GHC + t] + S[S_GH2 + t];
+        if (t < J) { shc[t] = S[S_GCS + t]; shs[t] = S[S_GSN + t]; }
+        if (t == 0) jsolve = 0;
+        double hn2 = slot_sum(R, R_GN, red);  // its barriers order the LDS reads below
         if (t == 0) {
-            const int m = I[I_GM];
-            const int J = I[I_GJ];
-            SEM_GLOBAL double* H = S + S_GH;
-            SEM_GLOBAL double* cs = S + S_GCS;
-            SEM_GLOBAL double* sn = S + S_GSN;
             SEM_GLOBAL double* gg = S + S_GG;
             const double hn = sqrt(hn2);
-            for (int i = 0; i <= J; ++i) H[i * m + J] = S[S_GHC + i] + S[S_GH2 + i];
-            H[(J + 1) * m + J] = hn;
+            double x = sums[0];
             for (int i = 0; i < J; ++i) {
-                const double x = H[i * m + J], y = H[(i + 1) * m + J];
-                H[i * m + J] = cs[i] * x + sn[i] * y;
-                H[(i + 1) * m + J] = -sn[i] * x + cs[i] * y;
+                const double y = sums[i + 1], c = shc[i], s = shs[i];
+                sums[i] = fma(c, x, s * y);
+                x = fma(c, y, -(s * x));
             }
-            const double x = H[J * m + J], y = H[(J + 1) * m + J];
-            const double den = sqrt(x * x + y * y);
-            cs[J] = x / den;
-            sn[J] = y / den;
-            H[J * m + J] = den;
+            const double den = sqrt(fma(x, x, hn * hn));
+            const double cj = x / den, sj = hn / den, gj = gg[J];
+            sums[J] = den;
             H[(J + 1) * m + J] = 0.0;
-            gg[J + 1] = -sn[J] * gg[J];
-            gg[J] = cs[J] * gg[J];
+            S[S_GCS + J] = cj;
+            S[S_GSN + J] = sj;
+            const double gn = -sj * gj;
+            gg[J + 1] = gn;
+            gg[J] = cj * gj;
             I[I_GIT] += 1;
-            const bool bad = !finite(gg[J + 1]) || !finite(den);
+            const bool bad = !finite(gn) || !finite(den);
             if (bad) I[I_NAN] = 1;
-            if (bad || fabs(gg[J + 1]) <= S[S_PTOL] || hn == 0.0 || J + 1 == m || I[I_GIT] >= I[I_GMAXIT]) {
+            if (bad || fabs(gn) <= S[S_PTOL] || hn == 0.0 || J + 1 == m || I[I_GIT] >= I[I_GMAXIT]) {
                 const int jend = bad ? 0 : J + 1;
-                SEM_GLOBAL double* yv = S + S_GY;
-                for (int r = jend - 1; r >= 0; --r) {
-                    double s = gg[r];
-                    for (int k = r + 1; k < jend; ++k) s -= H[r * m + k] * yv[k];
-                    yv[r] = s / H[r * m + r];
-                }
+                jsolve = jend;
                 I[I_GJEND] = jend;
                 I[I_GARN] = 0;
                 I[I_GEND] = 1;
@@ -241,6 +277,27 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
                 I[I_GJ] = J + 1;
                 S[S_GVS + J + 1] = 1.0 / hn;
                 I[I_GNORM] = 1;
+            }
+        }
+        __syncthreads();
+        if (t <= J) H[t * m + J] = sums[t];
+        const int n = jsolve;  // uniform
+        if (n > 0) {
+            // y from the upper triangular system (column J is still in LDS)
+            double* sH = stage;
+            for (int q = t; q < n * n; q += blockDim.x) {
+                const int r = q / n, c = q - r * n;
+                sH[r * SEM_MAXM + c] = c == J ? sums[r] : r <= c ? H[r * m + c] : 0.0;
+            }
+            if (t < n) shc[t] = S[S_GG + t];
+            __syncthreads();
+            if (t == 0) {
+                for (int r = n - 1; r >= 0; --r) {
+                    double s = shc[r];
+                    for (int k = r + 1; k < n; ++k) s -= sH[r * SEM_MAXM + k] * shs[k];
+                    shs[r] = s / sH[r * SEM_MAXM + r];
+                    S[S_GY + r] = shs[r];
+                }
             }
         }
         break;
@@ -259,8 +316,7 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
             } else {
                 I[I_GJ] = 0;
                 SEM_GLOBAL double* gg = S + S_GG;
-                for (int i = 0; i <= SEM_MAXM; ++i) gg[i] = 0.0;
-                gg[0] = beta;
+                gg[0] = beta;  // (gg[j + 1] is written with column j, before it is read)
                 S[S_GVS] = 1.0 / beta;
                 I[I_GARN] = 1; I[I_GNORM] = 1;
             }
@@ -279,7 +335,7 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
     }
     case FIN_PR_ALPHA: {
         const int l = I[I_PRL];
-        multi_slot_sum(R, R_GM, l, sums, scratch);
+        multi_slot_sum(R, R_GM, l, sums, stage);
         if (t < l) S[S_PRA + t] = sums[t] * S[S_PRS + t];
         break;
     }
@@ -293,15 +349,17 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
     }
     case FIN_PR_BETA: {
         const int l = I[I_PRL];
-        multi_slot_sum(R, R_GM, l + 1, sums, scratch);
+        multi_slot_sum(R, R_GM, l + 1, sums, stage);
+        if (t < l) {
+            const double bi = sums[t] * S[S_PRS + t];
+            S[S_PRB + t] = bi;
+            shc[t] = bi;
+        }
+        __syncthreads();
         if (t == 0) {
             const double n2b = sums[l];
             double n2 = n2b;
-            for (int i = 0; i < l; ++i) {
-                const double bi = sums[i] * S[S_PRS + i];
-                S[S_PRB + i] = bi;
-                n2 -= bi * bi;
-            }
+            for (int i = 0; i < l; ++i) n2 -= shc[i] * shc[i];
             // a vector whose A-norm mostly lies in the space is dependent: dropped
             const int add = finite(n2b) && n2b > 0.0 && n2 > 1e-12 * n2b;
             I[I_PRADD] = add;
@@ -456,7 +514,6 @@ static __device__ __noinline__ void fin_body(ReqDesc* R, int ri, const FinArgs a
     }
     default: break;
     }
-    (void)sums;
 }
 
 

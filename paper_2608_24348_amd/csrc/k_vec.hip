@@ -406,8 +406,9 @@ __device__ __forceinline__ void gm_body(const ReqDesc* R, const PtRange& pr, dou
 template <int MODE, typename TB>
 __global__ void __launch_bounds__(SEM_VEC_THREADS) gm_pass_kernel(Batch bt, int gate)
 {
-    constexpr int NV = SEM_MAXM + 1;
-    __shared__ double red[(SEM_VEC_THREADS / 64) * NV];
+    constexpr int NV = SEM_MAXM + 1, NW = SEM_VEC_THREADS / 64, RS = 32;
+    __shared__ double red[NW * RS];
+    __shared__ double redm[NW];
     const int g = blockIdx.x;
     const int ri = find_req(bt.vb, bt.n, g);
     const ReqDesc* R = bt.r[ri];
@@ -425,26 +426,33 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) gm_pass_kernel(Batch bt, int 
 #undef GM_CASE
     default: break;
     }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int nv = MODE == 2 ? 1 : J + 1;
+    if constexpr (MODE == 2) {
+        const double s = wave_sum(acc[0]);
+        if (lane == 0) red[wid * RS] = s;
+    } else {
+        double v[RS];
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-        if (i < nv) acc[i] = wave_sum(acc[i]);
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (i < nv) red[wid * NV + i] = acc[i];
+        for (int i = 0; i < RS; ++i) v[i] = i < NV ? acc[i] : 0.0;
+        wave_sums(v, nv, red + wid * RS);
+    }
+    if constexpr (MODE == 0) {
+        accm = wave_sum(accm);
+        if (lane == 0) redm[wid] = accm;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < nv; i += blockDim.x) {
         double s = 0;
-        for (int w = 0; w < nw; ++w) s += red[w * NV + i];
+        for (int w = 0; w < NW; ++w) s += red[w * RS + i];
         put_partial(R, MODE == 2 ? R_GN : R_GM + i, blk, s);
     }
-    if (MODE == 0) {
-        double v1[1] = {accm};
-        block_sum<double, 1>(v1, red);
-        if (threadIdx.x == 0) put_partial(R, R_GMEAN, blk, v1[0]);
+    if constexpr (MODE == 0) {
+        if (threadIdx.x == 64) {
+            double s = 0;
+            for (int w = 0; w < NW; ++w) s += redm[w];
+            put_partial(R, R_GMEAN, blk, s);
+        }
     }
 }
 
@@ -508,8 +516,8 @@ __device__ __forceinline__ void pr_body(const ReqDesc* R, const PtRange& pr, dou
 template <int MODE, typename TB>
 __global__ void __launch_bounds__(SEM_VEC_THREADS) pr_pass_kernel(Batch bt, int gate)
 {
-    constexpr int NV = SEM_MAX_PROJ + 1;
-    __shared__ double red[(SEM_VEC_THREADS / 64) * NV];
+    constexpr int NV = SEM_MAX_PROJ + 1, NW = SEM_VEC_THREADS / 64, RS = (NV + 3) / 4 * 4;
+    __shared__ double red[NW * RS];
     const int g = blockIdx.x;
     const int ri = find_req(bt.vb, bt.n, g);
     const ReqDesc* R = bt.r[ri];
@@ -527,20 +535,15 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) pr_pass_kernel(Batch bt, int 
     default: break;
     }
     if (MODE == 0 || MODE == 2) {
-        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
         const int nv = MODE == 0 ? l : l + 1;
+        double v[RS];
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
-            if (i < nv) acc[i] = wave_sum(acc[i]);
-        if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < NV; ++i)
-                if (i < nv) red[wid * NV + i] = acc[i];
-        }
+        for (int i = 0; i < RS; ++i) v[i] = i < NV ? acc[i] : 0.0;
+        wave_sums(v, nv, red + (threadIdx.x >> 6) * RS);
         __syncthreads();
         for (int i = threadIdx.x; i < nv; i += blockDim.x) {
             double sum = 0;
-            for (int q = 0; q < nw; ++q) sum += red[q * NV + i];
+            for (int q = 0; q < NW; ++q) sum += red[q * RS + i];
             put_partial(R, R_GM + i, blk, sum);
         }
     }
@@ -654,7 +657,7 @@ void launch_vec(const Batch& b, const VecArgs& a, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ finalise kernel
-__global__ void __launch_bounds__(256) fin_kernel(Batch bt, FinArgs a)
+__global__ void __launch_bounds__(SEM_FIN_THREADS) fin_kernel(Batch bt, FinArgs a)
 {
     fin_body((ReqDesc*)bt.r[blockIdx.x], blockIdx.x, a);
 }
@@ -662,7 +665,7 @@ __global__ void __launch_bounds__(256) fin_kernel(Batch bt, FinArgs a)
 void launch_fin(const Batch& b, const FinArgs& a, hipStream_t s)
 {
     if (b.n == 0) return;
-    hipLaunchKernelGGL(fin_kernel, dim3(b.n), dim3(256), 0, s, b, a);
+    hipLaunchKernelGGL(fin_kernel, dim3(b.n), dim3(SEM_FIN_THREADS), 0, s, b, a);
 }
 
 }  // namespace semk

@@ -20,6 +20,7 @@
 #define SEM_MAXM 30          // largest GMRES restart length
 #define SEM_GS_THREADS 256   // threads of the gather-scatter kernel
 #define SEM_VEC_THREADS 256  // threads of point-wise kernels
+#define SEM_FIN_THREADS 512  // threads of the one-workgroup finaliser of a request
 #define HS_NELMAX 64         // HSMG: elements per direction at most (a coarse plane fits in LDS)
 #define HS_CPLANE (HS_NELMAX * HS_NELMAX)
 
