@@ -22,6 +22,17 @@ template <typename T> __device__ __forceinline__ SEM_GLOBAL T* gfieldw(const Req
     return (SEM_GLOBAL T*)R->f[id];
 }
 
+// input or output component c of a standalone operator's arrays, else the
+// request's field id + c
+__device__ __forceinline__ const SEM_GLOBAL double* op_in(const ReqDesc* R, const OpArrays& io, int id, int c)
+{
+    return io.in[0] ? gp(io.in[c]) : gfield<double>(R, id + c);
+}
+__device__ __forceinline__ SEM_GLOBAL double* op_out(const ReqDesc* R, const OpArrays& io, int id, int c)
+{
+    return io.out[0] ? gp(io.out[c]) : gfieldw<double>(R, id + c);
+}
+
 // Workgroup barrier for LDS producer/consumer hand-offs only: waits for this
 // wave's LDS operations (lgkmcnt) but not for its outstanding global loads,
 // so prefetched HBM data stays in flight across the barrier (__syncthreads()

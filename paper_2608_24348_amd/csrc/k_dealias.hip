@@ -232,7 +232,7 @@ template <typename TM, typename C> __device__ __forceinline__ C mscale(const Req
 
 // BN = dealiased -B (u . grad) u of the velocity field (F_U), fp64 output
 template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(Dl<LX>::NT) conv_dealias_kernel(Batch bt)
+__global__ void __launch_bounds__(Dl<LX>::NT) conv_dealias_kernel(Batch bt, OpArrays io)
 {
     constexpr int LXD = Dl<LX>::LXD, N3 = Dl<LX>::N3, ND3 = Dl<LX>::ND3, NT = Dl<LX>::NT, NQ = Dl<LX>::NQ;
     __shared__ C sI[LXD * LX], sID[LXD * LX];
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(Dl<LX>::NT) conv_dealias_kernel(Batch bt)
     const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
     const SEM_GLOBAL double* U[3];
     SEM_GLOBAL double* O[3];
-    for (int c = 0; c < 3; ++c) { U[c] = gfield<double>(R, F_U + c); O[c] = gfieldw<double>(R, F_BN + c); }
+    for (int c = 0; c < 3; ++c) { U[c] = op_in(R, io, F_U, c); O[c] = op_out(R, io, F_BN, c); }
     __syncthreads();
     for (int el = 0; el < R->epb; ++el) {
         const int e = blk * R->epb + el;
@@ -353,7 +353,7 @@ template <int LX> struct Dm {
 };
 
 template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(Dm<LX>::NT) conv_dealias_mfma_kernel(Batch bt)
+__global__ void __launch_bounds__(Dm<LX>::NT) conv_dealias_mfma_kernel(Batch bt, OpArrays io)
 {
     using D = Dm<LX>;
     using M = Mma<C>;
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(Dm<LX>::NT) conv_dealias_mfma_kernel(Batch bt)
     const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
     const SEM_GLOBAL double* U[3];
     SEM_GLOBAL double* O[3];
-    for (int c = 0; c < 3; ++c) { U[c] = gfield<double>(R, F_U + c); O[c] = gfieldw<double>(R, F_BN + c); }
+    for (int c = 0; c < 3; ++c) { U[c] = op_in(R, io, F_U, c); O[c] = op_out(R, io, F_BN, c); }
     C* sY1 = R1;            // [2][NL][LXD]: P = I u, Q = ID u along the first index
     C* sT = R1;             // [LXD][NN]: weighted integrand at the fine points
     C* sZ2 = R1;            // [NL][LXD]
@@ -635,7 +635,7 @@ template <int LX, typename C> struct Dv2 {
 };
 
 template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__((Dv2<LX, C>::NT), (Dv2<LX, C>::WPE)) conv_dealias_v2_kernel(Batch bt)
+__global__ void __launch_bounds__((Dv2<LX, C>::NT), (Dv2<LX, C>::WPE)) conv_dealias_v2_kernel(Batch bt, OpArrays io)
 {
     using D = Dm<LX>;
     using Q = Dv2<LX, C>;
@@ -682,12 +682,12 @@ __global__ void __launch_bounds__((Dv2<LX, C>::NT), (Dv2<LX, C>::WPE)) conv_deal
         }
     }
     const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
-    const SEM_GLOBAL double* U0 = gfield<double>(R, F_U);
-    const SEM_GLOBAL double* U1 = gfield<double>(R, F_U1);
-    const SEM_GLOBAL double* U2 = gfield<double>(R, F_U2);
-    SEM_GLOBAL double* O0 = gfieldw<double>(R, F_BN);
-    SEM_GLOBAL double* O1 = gfieldw<double>(R, F_BNb);
-    SEM_GLOBAL double* O2 = gfieldw<double>(R, F_BNc);
+    const SEM_GLOBAL double* U0 = op_in(R, io, F_U, 0);
+    const SEM_GLOBAL double* U1 = op_in(R, io, F_U, 1);
+    const SEM_GLOBAL double* U2 = op_in(R, io, F_U, 2);
+    SEM_GLOBAL double* O0 = op_out(R, io, F_BN, 0);
+    SEM_GLOBAL double* O1 = op_out(R, io, F_BN, 1);
+    SEM_GLOBAL double* O2 = op_out(R, io, F_BN, 2);
 
     // the velocity of the next element is loaded while the current one is processed
     constexpr int NUP = Q::NUP;
@@ -898,18 +898,19 @@ void launch_dealias_geom(const Batch& b, int lx, const MeshParams& mp, int want3
 
 // metric storage tm and arithmetic tc (tables in the arithmetic precision):
 // (fp64, fp64), (fp32, fp64), (fp32, fp32) or (fp16/bf16, fp32)
-void launch_conv_dealias(const Batch& b, int lx, int tm, int tc, hipStream_t s)
+void launch_conv_dealias(const Batch& b, int lx, int tm, int tc, hipStream_t s, const OpArrays* arrays)
 {
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     if (b.eb[b.n] == 0) return;
     // matrix-core form while the fine grid fits one 16-row tile (lx <= 10)
 #define GO3(L, TM, C)                                                                                                  \
     do {                                                                                                               \
         if constexpr (Dv2<L, C>::fits)                                                                                 \
-            hipLaunchKernelGGL((conv_dealias_v2_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3((Dv2<L, C>::NT)), 0, s, b);  \
+            hipLaunchKernelGGL((conv_dealias_v2_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3((Dv2<L, C>::NT)), 0, s, b, io);  \
         else if constexpr ((3 * L + 1) / 2 <= 16)                                                                      \
-            hipLaunchKernelGGL((conv_dealias_mfma_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dm<L>::NT), 0, s, b);      \
+            hipLaunchKernelGGL((conv_dealias_mfma_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dm<L>::NT), 0, s, b, io);      \
         else                                                                                                           \
-            hipLaunchKernelGGL((conv_dealias_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dl<L>::NT), 0, s, b);           \
+            hipLaunchKernelGGL((conv_dealias_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dl<L>::NT), 0, s, b, io);           \
     } while (0)
     if (tm == P64) {
 #define GO(L) GO3(L, double, double)

@@ -68,7 +68,7 @@ __device__ __forceinline__ void load_D(const ReqDesc* R, C* sD)
 }
 
 template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt)
+__global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, OpArrays io)
 {
     OPS_PROLOGUE(LX)
     __shared__ C sD[L2];
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt)
     C col[3][LX];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const SEM_GLOBAL double* u = gfield<double>(R, F_U + c);
+        const SEM_GLOBAL double* u = op_in(R, io, F_U, c);
 #pragma unroll
         for (int k = 0; k < LX; ++k) col[c][k] = (C)u[ebase + k * L2 + ij];
     }
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt)
                 C s = 0;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) s += col[c][k] * (m[0 * 3 + c] * dr + m[1 * 3 + c] * ds + m[2 * 3 + c] * dt);
-                gfieldw<double>(R, F_BN + f)[ebase + p] = -(double)s;
+                op_out(R, io, F_BN, f)[ebase + p] = -(double)s;
             }
         }
         lds_handoff<OWave<LX>::v>();
@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt)
 //   rhs_c = sum_q a_q BN_c^{n-q} + (B / dt) sum_q b_q u_c^{n-q} - (grad p)_c,
 // so grad p is never written and read back (48 bytes per point)
 template <int LX, typename TM, typename C, bool RHS = false>
-__global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src, int dst)
+__global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src, int dst, OpArrays io)
 {
     OPS_PROLOGUE(LX)
     __shared__ C sD[L2];
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
-    const SEM_GLOBAL double* u = gfield<double>(R, src);
+    const SEM_GLOBAL double* u = op_in(R, io, src, 0);
     double a1 = 0, a2 = 0, a3 = 0, b1 = 0, b2 = 0, b3 = 0, idt = 0;
     if constexpr (RHS) {
         const SEM_GLOBAL double* S = gp(R->S);
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
                      + ldm<TM, C>(M, ((long long)ee * 9 + 1 * 3 + c) * L3 + p, msc) * ds
                      + ldm<TM, C>(M, ((long long)ee * 9 + 2 * 3 + c) * L3 + p, msc) * dt;
                 if constexpr (RHS) gfieldw<double>(R, F_RHS + c)[ebase + p] = ev[c] + (bv * idt) * hv[c] - (double)gc;
-                else gfieldw<double>(R, dst + c)[ebase + p] = (double)gc;
+                else op_out(R, io, dst, c)[ebase + p] = (double)gc;
             }
         }
         lds_handoff<OWave<LX>::v>();
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
 }
 
 template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, int dst)
+__global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, int dst, OpArrays io)
 {
     OPS_PROLOGUE(LX)
     __shared__ C sD[L2];
@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
         if (live) {
             C v[3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[c] = (C)gfield<double>(R, src + c)[ebase + p];
+            for (int c = 0; c < 3; ++c) v[c] = (C)op_in(R, io, src, c)[ebase + p];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
         lds_handoff<OWave<LX>::v>();
     }
     if (live) {
-        SEM_GLOBAL double* out = gfieldw<double>(R, dst);
+        SEM_GLOBAL double* out = op_out(R, io, dst, 0);
 #pragma unroll
         for (int k = 0; k < LX; ++k) out[ebase + k * L2 + ij] = (double)wacc[k];
     }
@@ -343,40 +343,44 @@ __global__ void __launch_bounds__(ONthr<LX>::v) diagnostics_kernel(Batch bt)
     else if (tm == P16) hipLaunchKernelGGL((KERNEL<L, __half, float>), grid, blk, 0, s, __VA_ARGS__);             \
     else hipLaunchKernelGGL((KERNEL<L, __hip_bfloat16, float>), grid, blk, 0, s, __VA_ARGS__);
 
-void launch_conv(const Batch& b, int lx, int tm, int tc, hipStream_t s)
+void launch_conv(const Batch& b, int lx, int tm, int tc, hipStream_t s, const OpArrays* arrays)
 {
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(conv_kernel, L, grid, dim3(ONthr<L>::v), s, b)
+#define GO(L) OPS_DISPATCH(conv_kernel, L, grid, dim3(ONthr<L>::v), s, b, io)
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
-void launch_opgrad(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s)
+void launch_opgrad(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const OpArrays* arrays)
 {
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(opgrad_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst)
+#define GO(L) OPS_DISPATCH(opgrad_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io)
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
 void launch_opgrad_rhs(const Batch& b, int lx, int tm, int tc, int src, hipStream_t s)
 {
+    const OpArrays io = {};
     dim3 grid(b.eb[b.n]);
 #define GO(L)                                                                                                          \
-    if (tm == P64) hipLaunchKernelGGL((opgrad_kernel<L, double, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1); \
+    if (tm == P64) hipLaunchKernelGGL((opgrad_kernel<L, double, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
     else if (tm == P32 && tc == P64)                                                                                   \
-        hipLaunchKernelGGL((opgrad_kernel<L, float, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1);       \
-    else if (tm == P32) hipLaunchKernelGGL((opgrad_kernel<L, float, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1); \
-    else if (tm == P16) hipLaunchKernelGGL((opgrad_kernel<L, __half, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1); \
-    else hipLaunchKernelGGL((opgrad_kernel<L, __hip_bfloat16, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1);
+        hipLaunchKernelGGL((opgrad_kernel<L, float, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io);       \
+    else if (tm == P32) hipLaunchKernelGGL((opgrad_kernel<L, float, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
+    else if (tm == P16) hipLaunchKernelGGL((opgrad_kernel<L, __half, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
+    else hipLaunchKernelGGL((opgrad_kernel<L, __hip_bfloat16, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io);
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
-void launch_wdiv(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s)
+void launch_wdiv(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const OpArrays* arrays)
 {
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(wdiv_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst)
+#define GO(L) OPS_DISPATCH(wdiv_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io)
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }

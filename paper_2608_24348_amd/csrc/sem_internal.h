@@ -313,6 +313,14 @@ struct AxLaunch {
     void* w_raw;
 };
 
+// Caller arrays of a standalone element operator (fp64, E*lx^3 values each);
+// null: the request's own fields.  The kernels read and write them in place of
+// staging copies, so no output may overlap an input or another output.
+struct OpArrays {
+    const double* in[3];
+    double* out[3];
+};
+
 void launch_ax(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
 // the matrix-core operator (lx = 8, fp32 arithmetic, 16-bit geometry, no Jacobi
 // scaling, residual form or fp64 output); false when it does not apply
@@ -321,6 +329,8 @@ bool launch_ax_mfma(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
 // as per-workgroup partials in slot pslot + c (see gs_blocks for their count)
 void launch_dssum(const Batch& b, int field, int ncomp, int tprec, int gate, void* raw, hipStream_t s,
                   int pslot = -1);
+// out = dssum(B o f) in one pass, fp64 arrays of one request (out == f or disjoint)
+void launch_mass_dssum(const Batch& b, const double* f, double* out, hipStream_t s);
 
 // geometry and setup
 void launch_geometry(const Batch& b, int lx, const MeshParams& mp, hipStream_t s);
@@ -331,13 +341,15 @@ void launch_init_fields(const Batch& b, int lx, int init, const MeshParams& mp, 
 void launch_node_field(const Batch& b, int lx, const MeshParams& mp, int what, double amp, double* out, hipStream_t s);
 
 // SEM operators (output fp64)
-void launch_conv(const Batch& b, int lx, int tm, int tc, hipStream_t s);
+void launch_conv(const Batch& b, int lx, int tm, int tc, hipStream_t s, const OpArrays* io = nullptr);
 void launch_dealias_geom(const Batch& b, int lx, const MeshParams& mp, int want32, int want16, hipStream_t s);
-void launch_conv_dealias(const Batch& b, int lx, int tm, int tc, hipStream_t s);
-void launch_opgrad(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s);
+void launch_conv_dealias(const Batch& b, int lx, int tm, int tc, hipStream_t s, const OpArrays* io = nullptr);
+void launch_opgrad(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s,
+                   const OpArrays* io = nullptr);
 // grad p folded into the step's local velocity rhs (F_RHS), without storing grad p
 void launch_opgrad_rhs(const Batch& b, int lx, int tm, int tc, int src, hipStream_t s);
-void launch_wdiv(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s);
+void launch_wdiv(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s,
+                 const OpArrays* io = nullptr);
 void launch_diagnostics(const Batch& b, int lx, hipStream_t s);
 
 // HSMG in the Arnoldi step: z = M^{-1} s_J V_J into F_HZ (the operator's
