@@ -372,7 +372,7 @@ void launch_ax(const Batch& b, int lx, const AxLaunch& a0, hipStream_t s)
 {
     AxLaunch a = a0;
     if (a.ncomp < 1) a.ncomp = 1;
-    if (launch_ax_mfma(b, lx, a, s)) return;
+    if (launch_ax_mfma(b, lx, a, s) || launch_ax_wide(b, lx, a, s)) return;
     switch (lx) {
     case 3: ax_lx<3>(b, a, s); break;
     case 4: ax_lx<4>(b, a, s); break;
@@ -380,10 +380,6 @@ void launch_ax(const Batch& b, int lx, const AxLaunch& a0, hipStream_t s)
     case 6: ax_lx<6>(b, a, s); break;
     case 7: ax_lx<7>(b, a, s); break;
     case 8: ax_lx<8>(b, a, s); break;
-    case 9: ax_lx<9>(b, a, s); break;
-    case 10: ax_lx<10>(b, a, s); break;
-    case 11: ax_lx<11>(b, a, s); break;
-    case 12: ax_lx<12>(b, a, s); break;
     default: break;
     }
 }

@@ -1,0 +1,433 @@
+// Helmholtz/Poisson operator on matrix cores for lx = 9..12 (N = 8..11):
+//   w = h1 sum_ab D_a^T (G_ab o D_b u) + h2 B o u,  one wave per element.
+//
+// A wave holds its element's layers k as 16 x 16 tiles, rows j, columns i, in
+// the accumulator layout of the 16x16x4 MFMA: lane (g = lane / 16, m = lane %
+// 16) holds j = g + 4 r, i = m, r = 0..2.  Per layer:
+//  - j-derivative  D U:    the tile as held is the B operand of step s (rows
+//    j = 4 s + g), D the A operand, in registers for the whole kernel;
+//  - i-derivative  U D^T:  U is the A operand, read transposed from the wave's
+//    LDS;
+//  - k-derivative: every lane holds whole columns, so it is a sum over the
+//    layers in registers with uniform coefficients D[k][l];
+//  - the six G_ab multiply point by point, and the transposed contractions
+//    over i and j go through LDS into one chain of MFMA steps.
+// MFMA adds its four products in ascending order, each with one rounding, so a
+// chain of steps is the chain of fused multiply-adds of the column kernel
+// (k_ax.hip).  The transposed contractions alternate i- and j-terms per index
+// there; here the four products of a step are (l, i), (l, j), (l+1, i), (l+1,
+// j).  Every result has the bits of the column kernel, which walked k with one
+// thread per column and read 4 lx LDS values per point: LDS held it to 2.0 TB/s
+// (three fp64 components, 16^3 elements, lx = 12: 363 us) and 1.5 TB/s in fp32.
+// Here a tile of lx * lx points takes 18 LDS accesses of a wave.
+//
+// For fp32 the accumulator rows are 4 g + r; the rows of the A operand are
+// permuted (row m holds j = m / 4 + 4 (m % 4)) so that the layout is the same.
+#include "k_common.h"
+
+#include <type_traits>
+
+namespace semk {
+
+template <typename C> struct WMma;
+template <> struct WMma<double> {
+    typedef double V4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V4 mma(double a, double b, V4 c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int arow(int m) { return m; }
+};
+template <> struct WMma<float> {
+    typedef float V4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V4 mma(float a, float b, V4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int arow(int m) { return (m >> 2) + 4 * (m & 3); }
+};
+
+template <typename TG> struct AxwGeo {
+    static constexpr int g = F_G16, b = F_B16;
+};
+template <> struct AxwGeo<double> {
+    static constexpr int g = F_G64, b = F_B64;
+};
+template <> struct AxwGeo<float> {
+    static constexpr int g = F_G32, b = F_B32;
+};
+
+// a value rounded to the 16-bit format H16 names (1 fp16, 2 bf16) and back
+template <int H16, typename C> __device__ __forceinline__ C axw_r16(C x)
+{
+    if constexpr (H16 == 1) return (C)(float)(_Float16)(float)x;
+    else if constexpr (H16 == 2) return (C)(float)(__bf16)(float)x;
+    else return x;
+}
+
+// element c + off of a uniform array: a scalar base and a 32-bit lane offset, so
+// that the many layers of a wave share their address registers
+template <typename T> __device__ __forceinline__ const SEM_GLOBAL T* at(const SEM_GLOBAL T* base, int c, unsigned off)
+{
+    return (const SEM_GLOBAL T*)((const SEM_GLOBAL char*)(base + c) + (unsigned)(off * sizeof(T)));
+}
+template <typename T> __device__ __forceinline__ SEM_GLOBAL T* at(SEM_GLOBAL T* base, int c, unsigned off)
+{
+    return (SEM_GLOBAL T*)((SEM_GLOBAL char*)(base + c) + (unsigned)(off * sizeof(T)));
+}
+
+// Template parameters as ax_kernel (k_ax.hip): storage types of vectors TU and
+// geometry TG, arithmetic C, PC Jacobi scaling of the input (1 fp64, 2 fp32
+// diagonal), TW output, SUB residual form, H16 16-bit arithmetic, SHG geometry
+// shared by the components through L2.
+template <int LX, typename TU, typename TG, typename C, int PC, typename TW, int SUB = 0, int H16 = 0, int SHG = 0>
+__global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLaunch a)
+{
+    using M = WMma<C>;
+    typedef typename M::V4 V4;
+    constexpr int EPB = epb_of(LX), L2 = LX * LX, L3 = L2 * LX;
+    constexpr int NR = 3, KS = 3, KB = (LX + 1) / 2;
+    constexpr int NCOL = (L2 * EPB + 63) / 64 * 64;  // columns of the block, as the partial sums group them
+    constexpr int TS = 16 * LX + 16;                 // one tile in LDS, with room for the reads of unused lanes
+    constexpr int SCR = 3 * TS, WS = SCR + 64;       // a wave's LDS: u, w_r, w_s, a slot per lane for unused stores
+    static_assert(LX > 8 && LX <= 12, "three accumulator rows per lane");
+    __shared__ __align__(16) C lds[EPB * WS];
+    __shared__ C sD[H16 ? L2 : 1];
+    __shared__ double red[NCOL / 64];
+    static_assert(sizeof(double) * NCOL <= sizeof(C) * EPB * WS, "column dots reuse the tiles");
+
+    // components of an element block on one XCD back to back, as ax_kernel
+    const int bx = blockIdx.x;
+    const int comp = (bx / 8) % a.ncomp;
+    const int gb = (bx / (8 * a.ncomp)) * 8 + (bx & 7);
+    if (gb >= bt.eb[bt.n]) return;
+    const int ri = find_req(bt.eb, bt.n, gb);
+    const ReqDesc* R = bt.r[ri];
+    const int blk = gb - bt.eb[ri];
+    if (!gate_ok(R, a.gate < 0 ? -1 : a.gate + comp)) return;
+
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, g = lane >> 4, m = lane & 15;
+    const int e = blk * EPB + w;
+    const bool live = e < R->E;
+    const int ee = live ? e : 0;  // a wave without an element works on element 0 and stores nothing
+    if constexpr (H16 != 0) {
+        for (int q = t; q < L2; q += 64 * EPB) sD[q] = axw_r16<H16>(gp(R->D32)[q]);
+        block_sync_lds();
+    }
+
+    const SEM_GLOBAL TU* u = a.src_vj ? gfield<TU>(R, F_V) + (long long)gp(R->I)[I_GJ] * R->np
+                                      : a.src >= 0 ? gfield<TU>(R, a.src + comp) : gp((const TU*)a.u_raw);
+    SEM_GLOBAL TW* wo = a.dst >= 0 ? gfieldw<TW>(R, a.dst + comp) : gp((TW*)a.w_raw);
+    using TPC = typename std::conditional<PC == 2, float, double>::type;
+    C h1, h2;
+    if (a.hsel >= 0) { h1 = (C)gp(R->S)[a.hsel]; h2 = (C)gp(R->S)[a.hsel + 1]; }
+    else { h1 = (C)a.h1; h2 = (C)a.h2; }
+    if (a.src_vj) h1 *= (C)gp(R->S)[S_GVS + gp(R->I)[I_GJ]];
+    C gsc = (C)1, bsc = (C)1;
+    const bool helm = h2 != (C)0;
+    if constexpr (sizeof(TG) == 2) {
+        const SEM_GLOBAL float* sc = gfield<float>(R, F_GSC);
+        gsc = (C)sc[ee];
+        bsc = (C)sc[R->E + ee];
+    }
+    const C gmul = H16 ? (C)1 : gsc;
+
+    // the lane's three points of a layer: offsets in the element (unused lanes
+    // and rows read an existing point of it) and in the LDS tile
+    bool ok[NR];
+    unsigned off[NR];
+    int tix[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int j = g + 4 * r;
+        ok[r] = m < LX && j < LX;
+        off[r] = (j < LX ? j : LX - 1) * LX + (m < LX ? m : LX - 1);
+        tix[r] = ok[r] ? j * LX + m : SCR + lane;
+    }
+    const SEM_GLOBAL TU* ue = u + (long long)ee * L3;
+    const SEM_GLOBAL TG* Ge = gfield<TG>(R, AxwGeo<TG>::g) + (long long)ee * 6 * L3;
+    const SEM_GLOBAL TG* Be = gfield<TG>(R, AxwGeo<TG>::b) + (long long)ee * L3;
+
+    // all columns of u (and of the diagonal) and the first layer of G
+    TU uraw[LX][NR];
+    TPC praw[PC ? LX : 1][NR];
+    TG graw[6][NR];
+#pragma unroll
+    for (int k = 0; k < LX; ++k)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) uraw[k][r] = ldg(at(ue, k * L2, off[r]));
+    if constexpr (PC != 0) {
+        const SEM_GLOBAL TPC* pe = gfield<TPC>(R, a.precond) + (long long)ee * L3;
+#pragma unroll
+        for (int k = 0; k < LX; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) praw[k][r] = ldg(at(pe, k * L2, off[r]));
+    }
+    auto gload = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const SEM_GLOBAL TG* p = at(Ge, q * L3 + k * L2, off[r]);
+                if constexpr (SHG != 0) graw[q][r] = ldg(p);
+                else graw[q][r] = ldg_stream(p);
+            }
+    };
+    gload(0);
+
+    // 1D matrices: cJ, cI (forward, rows j and columns i), cB (transposed: the
+    // lane's index l of step s is 2 s + g / 2, even g an i-term, odd g a j-term)
+    auto dmat = [&](int row, int col) -> C {
+        if (row >= LX || col >= LX) return (C)0;
+        if constexpr (sizeof(C) == 8) return (C)gp(R->D64)[row * LX + col];
+        else return axw_r16<H16>((C)gp(R->D32)[row * LX + col]);
+    };
+    const int mj = M::arow(m);
+    C cJ[KS], cI[KS], cB[KB];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) { cJ[s] = dmat(mj, 4 * s + g); cI[s] = dmat(m, 4 * s + g); }
+    const bool jterm = (g & 1) != 0;
+#pragma unroll
+    for (int s = 0; s < KB; ++s) cB[s] = dmat(2 * s + (g >> 1), jterm ? mj : m);
+    C* const st = lds + w * WS;
+    const int ubase = mj * LX + g;
+    const int bbase = jterm ? 2 * TS + (g >> 1) * LX + m : TS + mj * LX + (g >> 1);
+    const int bstep = jterm ? 2 * LX : 2;
+
+    C uin[H16 ? LX : 1][NR], ureg[LX][NR], wacc[LX][NR];
+#pragma unroll
+    for (int k = 0; k < LX; ++k)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            C v = to<C>(uraw[k][r]);
+            if constexpr (PC != 0) v *= (C)praw[k][r];
+            if (LX % 4 != 0 && r == NR - 1) v = g + 4 * r < LX ? v : (C)0;  // rows past the element add nothing
+            ureg[k][r] = v;
+            wacc[k][r] = (C)0;
+        }
+    C hscale = (C)1;
+    if constexpr (H16 != 0) {
+        float mx = 0.0f;
+#pragma unroll
+        for (int k = 0; k < LX; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) mx = fmaxf(mx, ok[r] ? fabsf((float)ureg[k][r]) : 0.0f);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        float sc = 1.0f;
+        if (mx > 0.0f && mx < INFINITY) {
+            int ex;
+            (void)frexpf(mx, &ex);
+            sc = ldexpf(1.0f, -ex);
+        }
+        hscale = (C)(1.0f / sc);
+#pragma unroll
+        for (int k = 0; k < LX; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                uin[k][r] = ureg[k][r];
+                ureg[k][r] = axw_r16<H16>(ureg[k][r] * sc);
+            }
+    }
+
+    // uniform coefficients D[k][.]: scalar loads (the table does not change)
+    typedef const __attribute__((address_space(4))) C* CP;
+    const uintptr_t dp = sizeof(C) == 8 ? (uintptr_t)R->D64 : (uintptr_t)R->D32;
+    unsigned dlo = __builtin_amdgcn_readfirstlane((unsigned)dp), dhi = __builtin_amdgcn_readfirstlane((unsigned)(dp >> 32));
+
+#pragma unroll
+    for (int k = 0; k < LX; ++k) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) st[tix[r]] = ureg[k][r];
+        // (keeps each layer's coefficients from being loaded ahead of it)
+        asm volatile("" : "+s"(dlo), "+s"(dhi));
+        const CP Dt = (CP)((uintptr_t)dlo | ((uintptr_t)dhi << 32));
+        C dk[LX];
+#pragma unroll
+        for (int l = 0; l < LX; ++l) dk[l] = H16 ? sD[H16 ? k * LX + l : 0] : Dt[k * LX + l];
+        lds_handoff<true>();
+        C ut_[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            ut_[s] = st[ubase + 4 * s];
+            if (LX % 4 != 0 && s == KS - 1) ut_[s] = 4 * s + g < LX ? ut_[s] : (C)0;
+        }
+        V4 ur = {0, 0, 0, 0}, us = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            us = M::mma(cJ[s], ureg[k][s], us);
+            ur = M::mma(ut_[s], cI[s], ur);
+        }
+        C wt[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            C ut = 0;
+#pragma unroll
+            for (int l = 0; l < LX; ++l) ut += dk[l] * ureg[l][r];
+            C g6[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) g6[q] = to<C>(graw[q][r]) * gmul;
+            const C wr = axw_r16<H16>(g6[0] * ur[r] + g6[1] * us[r] + g6[2] * ut);
+            const C ws = axw_r16<H16>(g6[1] * ur[r] + g6[3] * us[r] + g6[4] * ut);
+            wt[r] = axw_r16<H16>(g6[2] * ur[r] + g6[4] * us[r] + g6[5] * ut);
+            st[TS + tix[r] - (ok[r] ? 0 : TS)] = wr;
+            st[2 * TS + tix[r] - (ok[r] ? 0 : 2 * TS)] = ws;
+        }
+        if (k + 1 < LX) gload(k + 1);
+#pragma unroll
+        for (int l = 0; l < LX; ++l)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) wacc[l][r] += dk[l] * wt[r];
+        lds_handoff<true>();
+        V4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KB; ++s) {
+            C v = st[bbase + s * bstep];
+            if (LX % 2 != 0 && s == KB - 1) v = 2 * s + (g >> 1) < LX ? v : (C)0;
+            acc = M::mma(jterm ? cB[s] : v, jterm ? v : cB[s], acc);
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r) wacc[k][r] += acc[r];
+        // the layer's sums are formed here, not kept as operands for later,
+        // and the lane offsets stay 32-bit operands of scalar-base loads
+#pragma unroll
+        for (int l = 0; l < LX; ++l)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(wacc[l][r]));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(off[r]));
+    }
+
+    double dot[NR] = {0.0, 0.0, 0.0};
+    const C hs = H16 ? h1 * (gsc * hscale) : h1;
+    const SEM_GLOBAL TW* rl = SUB ? gfield<TW>(R, a.sub + comp) + (long long)ee * L3 : nullptr;
+    SEM_GLOBAL TW* we = wo + (long long)ee * L3;
+    // the mass term and the local rhs are loaded only now, half the layers at a
+    // time: through the k-walk their registers would cost the second wave
+    constexpr int HB = (LX + 1) / 2;
+#pragma unroll
+    for (int k0 = 0; k0 < LX; k0 += HB) {
+        TG braw[HB][NR];
+        TW rraw[SUB ? HB : 1][NR];
+        if (helm) {
+#pragma unroll
+            for (int k = 0; k < HB; ++k)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (k0 + k < LX) braw[k][r] = ldg(at(Be, (k0 + k) * L2, off[r]));
+        }
+        if constexpr (SUB != 0) {
+#pragma unroll
+            for (int k = 0; k < HB; ++k)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (k0 + k < LX) rraw[k][r] = ldg(at(rl, (k0 + k) * L2, off[r]));
+        }
+#pragma unroll
+        for (int k = 0; k < HB; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                if (k0 + k >= LX) continue;
+                const int kk = k0 + k;
+                const C uk = H16 ? uin[H16 ? kk : 0][r] : ureg[kk][r];
+                const C bk = helm ? to<C>(braw[k][r]) * bsc : (C)0;
+                const C wv = hs * wacc[kk][r] + h2 * bk * uk;
+                const TW ws = SUB ? (TW)(rraw[SUB ? k : 0][r] - to<TW>(wv)) : to<TW>(wv);
+                if (live && ok[r]) stg(at(we, kk * L2, off[r]), ws);
+                if (a.pdot >= 0) dot[r] += (double)uk * (double)to<C>(ws);
+            }
+    }
+    if (a.pdot >= 0) {
+        // the columns' dots, summed in the order of the column kernel's threads
+        double* cd = (double*)lds;
+        block_sync_lds();
+        for (int q = EPB * L2 + t; q < NCOL; q += 64 * EPB) cd[q] = 0.0;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            if (ok[r]) cd[w * L2 + off[r]] = live ? dot[r] : 0.0;
+        block_sync_lds();
+        for (int q = w; q < NCOL / 64; q += EPB) {
+            const double s = wave_sum(cd[64 * q + lane]);
+            if (lane == 0) red[q] = s;
+        }
+        block_sync_lds();
+        if (t == 0) {
+            double s = 0.0;
+            for (int q = 0; q < NCOL / 64; ++q) s += red[q];
+            gp(R->part)[(long long)(a.pdot + comp) * R->pstride + blk] = s;
+            if (blk == 0) gp(R->I)[I_PCNT + a.pdot + comp] = R->nb;
+        }
+    }
+}
+
+template <int LX, typename TU, typename TG, typename C, int H16 = 0>
+static void axw_go(const Batch& b, const AxLaunch& a, hipStream_t s)
+{
+    const dim3 grid(((b.eb[b.n] + 7) / 8) * 8 * a.ncomp), blk(64 * epb_of(LX));
+    if constexpr (sizeof(TU) == 4) {
+        if (a.out64) {
+            if (a.precond >= 0 && a.tpc == P64)
+                hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 1, double, 0, H16>), grid, blk, 0, s, b, a);
+            else if (a.precond >= 0) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 2, double, 0, H16>), grid, blk, 0, s, b, a);
+            else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, double, 0, H16>), grid, blk, 0, s, b, a);
+            return;
+        }
+    }
+    if constexpr (sizeof(TU) == 8) {
+        if (a.precond >= 0 && a.tpc == P64) {
+            hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 1, TU, 0, H16>), grid, blk, 0, s, b, a);
+            return;
+        }
+        if (a.precond >= 0) {
+            hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 2, TU, 0, H16>), grid, blk, 0, s, b, a);
+            return;
+        }
+    }
+    if constexpr (sizeof(TU) == 8 && sizeof(TG) == 8 && sizeof(C) == 8 && H16 == 0) {
+        if (a.sub >= 0) {
+            if (a.ncomp > 1) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 1, 0, 1>), grid, blk, 0, s, b, a);
+            else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 1>), grid, blk, 0, s, b, a);
+            return;
+        }
+    }
+    if (a.ncomp > 1) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 0, H16, 1>), grid, blk, 0, s, b, a);
+    else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 0, H16>), grid, blk, 0, s, b, a);
+}
+
+// the (vector, geometry, arithmetic) combinations of ax_lx (k_ax.hip)
+template <int LX> static void axw_lx(const Batch& b, const AxLaunch& a, hipStream_t s)
+{
+    const int u = a.tu, g = a.tg, c = a.tc;
+    if (u == P64 && g == P64 && c == P64) axw_go<LX, double, double, double>(b, a, s);
+    else if (u == P64 && g == P32 && c == P64) axw_go<LX, double, float, double>(b, a, s);
+    else if (u == P64 && g == P16 && c == P64) axw_go<LX, double, __half, double>(b, a, s);
+    else if (u == P64 && g == PBF && c == P64) axw_go<LX, double, __hip_bfloat16, double>(b, a, s);
+    else if (u == P64 && g == P32 && c == P32) axw_go<LX, double, float, float>(b, a, s);
+    else if (u == P64 && g == P16 && c == P32) axw_go<LX, double, __half, float>(b, a, s);
+    else if (u == P64 && g == PBF && c == P32) axw_go<LX, double, __hip_bfloat16, float>(b, a, s);
+    else if (u == P32 && g == P32 && c == P64) axw_go<LX, float, float, double>(b, a, s);
+    else if (u == P32 && g == P16 && c == P64) axw_go<LX, float, __half, double>(b, a, s);
+    else if (u == P32 && g == PBF && c == P64) axw_go<LX, float, __hip_bfloat16, double>(b, a, s);
+    else if (u == P32 && g == P32 && c == P32) axw_go<LX, float, float, float>(b, a, s);
+    else if (u == P32 && g == P16 && c == P32) axw_go<LX, float, __half, float>(b, a, s);
+    else if (u == P32 && g == PBF && c == P32) axw_go<LX, float, __hip_bfloat16, float>(b, a, s);
+    else if (u == P16 && g == P16 && c == P32) axw_go<LX, __half, __half, float>(b, a, s);
+    else if (u == PBF && g == PBF && c == P32) axw_go<LX, __hip_bfloat16, __hip_bfloat16, float>(b, a, s);
+    else if (u == P32 && g == P16 && c == P16) axw_go<LX, float, __half, float, 1>(b, a, s);
+    else if (u == P16 && g == P16 && c == P16) axw_go<LX, __half, __half, float, 1>(b, a, s);
+    else if (u == P32 && g == PBF && c == PBF) axw_go<LX, float, __hip_bfloat16, float, 2>(b, a, s);
+    else if (u == PBF && g == PBF && c == PBF) axw_go<LX, __hip_bfloat16, __hip_bfloat16, float, 2>(b, a, s);
+}
+
+bool launch_ax_wide(const Batch& b, int lx, const AxLaunch& a, hipStream_t s)
+{
+    switch (lx) {
+    case 9: axw_lx<9>(b, a, s); return true;
+    case 10: axw_lx<10>(b, a, s); return true;
+    case 11: axw_lx<11>(b, a, s); return true;
+    case 12: axw_lx<12>(b, a, s); return true;
+    default: return false;
+    }
+}
+
+}  // namespace semk

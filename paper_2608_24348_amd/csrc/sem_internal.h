@@ -325,6 +325,8 @@ void launch_ax(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
 // the matrix-core operator (lx = 8, fp32 arithmetic, 16-bit geometry, no Jacobi
 // scaling, residual form or fp64 output); false when it does not apply
 bool launch_ax_mfma(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
+// the matrix-core operator of lx = 9..12, every form; false for other orders
+bool launch_ax_wide(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
 // pslot >= 0: also the squared norm over unique nodes of each component c,
 // as per-workgroup partials in slot pslot + c (see gs_blocks for their count)
 void launch_dssum(const Batch& b, int field, int ncomp, int tprec, int gate, void* raw, hipStream_t s,
