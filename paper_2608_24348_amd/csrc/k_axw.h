@@ -1,4 +1,5 @@
-// Helmholtz/Poisson operator on matrix cores for lx = 9..12 (N = 8..11):
+#pragma once
+// Helmholtz/Poisson operator on matrix cores for lx = 10..12 (N = 9..11):
 //   w = h1 sum_ab D_a^T (G_ab o D_b u) + h2 B o u,  one wave per element.
 //
 // A wave holds its element's layers k as 16 x 16 tiles, rows j, columns i, in
@@ -80,17 +81,28 @@ template <typename T> __device__ __forceinline__ SEM_GLOBAL T* at(SEM_GLOBAL T* 
 // geometry TG, arithmetic C, PC Jacobi scaling of the input (1 fp64, 2 fp32
 // diagonal), TW output, SUB residual form, H16 16-bit arithmetic, SHG geometry
 // shared by the components through L2.
-template <int LX, typename TU, typename TG, typename C, int PC, typename TW, int SUB = 0, int H16 = 0, int SHG = 0>
-__global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLaunch a)
+// Layers of G in flight (nb) and waves per SIMD that the registers must leave
+// room for (mw).  fp64 holds 246 VGPRs with one layer; a second layer would
+// cost the second wave (16^3, lx = 12: 209 us against 89).  fp32 at lx = 12:
+// two layers at two waves 43 us, one layer at three waves 46; at lx = 10, with
+// fewer points to a lane's registers, one layer at four waves 55 us against 57
+// with two at two (20^3).  16-bit arithmetic keeps more operands: lx = 10 68 us
+// at three waves, 80 at two; lx = 12 51 us at two, 54 at three.
+template <int LX, typename C, int H16> struct AxwDepth {
+    static constexpr int nb = sizeof(C) == 4 && !H16 && LX > 10 ? 2 : 1;
+    static constexpr int mw = sizeof(C) == 8 || LX > 10 ? 2 : H16 ? 3 : 4;
+};
+template <int LX, int WPB, typename TU, typename TG, typename C, int PC, typename TW, int SUB = 0, int H16 = 0, int SHG = 0>
+__global__ void __launch_bounds__(64 * WPB, (AxwDepth<LX, C, H16>::mw)) axw_kernel(Batch bt, AxLaunch a)
 {
     using M = WMma<C>;
     typedef typename M::V4 V4;
-    constexpr int EPB = epb_of(LX), L2 = LX * LX, L3 = L2 * LX;
+    constexpr int EPB = WPB, L2 = LX * LX, L3 = L2 * LX;
     constexpr int NR = 3, KS = 3, KB = (LX + 1) / 2;
     constexpr int NCOL = (L2 * EPB + 63) / 64 * 64;  // columns of the block, as the partial sums group them
     constexpr int TS = 16 * LX + 16;                 // one tile in LDS, with room for the reads of unused lanes
     constexpr int SCR = 3 * TS, WS = SCR + 64;       // a wave's LDS: u, w_r, w_s, a slot per lane for unused stores
-    static_assert(LX > 8 && LX <= 12, "three accumulator rows per lane");
+    static_assert(LX > 9 && LX <= 12, "three accumulator rows per lane");
     __shared__ __align__(16) C lds[EPB * WS];
     __shared__ C sD[H16 ? L2 : 1];
     __shared__ double red[NCOL / 64];
@@ -100,10 +112,11 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
     const int bx = blockIdx.x;
     const int comp = (bx / 8) % a.ncomp;
     const int gb = (bx / (8 * a.ncomp)) * 8 + (bx & 7);
-    if (gb >= bt.eb[bt.n]) return;
-    const int ri = find_req(bt.eb, bt.n, gb);
+    const int* const pre = WPB == 1 ? bt.el : bt.eb;
+    if (gb >= pre[bt.n]) return;
+    const int ri = find_req(pre, bt.n, gb);
     const ReqDesc* R = bt.r[ri];
-    const int blk = gb - bt.eb[ri];
+    const int blk = gb - pre[ri];
     if (!gate_ok(R, a.gate < 0 ? -1 : a.gate + comp)) return;
 
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, g = lane >> 4, m = lane & 15;
@@ -151,13 +164,14 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
     // all columns of u (and of the diagonal) and the first layer of G
     TU uraw[LX][NR];
     TPC praw[PC ? LX : 1][NR];
-    TG graw[6][NR];
+    constexpr int NB = AxwDepth<LX, C, H16>::nb;
+    TG graw[NB][6][NR];
 #pragma unroll
     for (int k = 0; k < LX; ++k)
 #pragma unroll
         for (int r = 0; r < NR; ++r) uraw[k][r] = ldg(at(ue, k * L2, off[r]));
+    const SEM_GLOBAL TPC* pe = PC ? gfield<TPC>(R, a.precond) + (long long)ee * L3 : nullptr;
     if constexpr (PC != 0) {
-        const SEM_GLOBAL TPC* pe = gfield<TPC>(R, a.precond) + (long long)ee * L3;
 #pragma unroll
         for (int k = 0; k < LX; ++k)
 #pragma unroll
@@ -169,11 +183,12 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
                 const SEM_GLOBAL TG* p = at(Ge, q * L3 + k * L2, off[r]);
-                if constexpr (SHG != 0) graw[q][r] = ldg(p);
-                else graw[q][r] = ldg_stream(p);
+                if constexpr (SHG != 0) graw[k % NB][q][r] = ldg(p);
+                else graw[k % NB][q][r] = ldg_stream(p);
             }
     };
-    gload(0);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) gload(k);
 
     // 1D matrices: cJ, cI (forward, rows j and columns i), cB (transposed: the
     // lane's index l of step s is 2 s + g / 2, even g an i-term, odd g a j-term)
@@ -194,7 +209,7 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
     const int bbase = jterm ? 2 * TS + (g >> 1) * LX + m : TS + mj * LX + (g >> 1);
     const int bstep = jterm ? 2 * LX : 2;
 
-    C uin[H16 ? LX : 1][NR], ureg[LX][NR], wacc[LX][NR];
+    C ureg[LX][NR], wacc[LX][NR];
 #pragma unroll
     for (int k = 0; k < LX; ++k)
 #pragma unroll
@@ -224,10 +239,7 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
 #pragma unroll
         for (int k = 0; k < LX; ++k)
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                uin[k][r] = ureg[k][r];
-                ureg[k][r] = axw_r16<H16>(ureg[k][r] * sc);
-            }
+            for (int r = 0; r < NR; ++r) ureg[k][r] = axw_r16<H16>(ureg[k][r] * sc);
     }
 
     // uniform coefficients D[k][.]: scalar loads (the table does not change)
@@ -266,14 +278,14 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
             for (int l = 0; l < LX; ++l) ut += dk[l] * ureg[l][r];
             C g6[6];
 #pragma unroll
-            for (int q = 0; q < 6; ++q) g6[q] = to<C>(graw[q][r]) * gmul;
+            for (int q = 0; q < 6; ++q) g6[q] = to<C>(graw[k % NB][q][r]) * gmul;
             const C wr = axw_r16<H16>(g6[0] * ur[r] + g6[1] * us[r] + g6[2] * ut);
             const C ws = axw_r16<H16>(g6[1] * ur[r] + g6[3] * us[r] + g6[4] * ut);
             wt[r] = axw_r16<H16>(g6[2] * ur[r] + g6[4] * us[r] + g6[5] * ut);
             st[TS + tix[r] - (ok[r] ? 0 : TS)] = wr;
             st[2 * TS + tix[r] - (ok[r] ? 0 : 2 * TS)] = ws;
         }
-        if (k + 1 < LX) gload(k + 1);
+        if (k + NB < LX) gload(k + NB);
 #pragma unroll
         for (int l = 0; l < LX; ++l)
 #pragma unroll
@@ -309,6 +321,20 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
     for (int k0 = 0; k0 < LX; k0 += HB) {
         TG braw[HB][NR];
         TW rraw[SUB ? HB : 1][NR];
+        // 16-bit arithmetic: the input as stored again (the registers hold its
+        // scaled rounding)
+        TU urd[H16 ? HB : 1][NR];
+        TPC prd[H16 && PC ? HB : 1][NR];
+        if constexpr (H16 != 0) {
+#pragma unroll
+            for (int k = 0; k < HB; ++k)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (k0 + k < LX) {
+                        urd[k][r] = ldg(at(ue, (k0 + k) * L2, off[r]));
+                        if constexpr (PC != 0) prd[k][r] = ldg(at(pe, (k0 + k) * L2, off[r]));
+                    }
+        }
         if (helm) {
 #pragma unroll
             for (int k = 0; k < HB; ++k)
@@ -329,7 +355,11 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
             for (int r = 0; r < NR; ++r) {
                 if (k0 + k >= LX) continue;
                 const int kk = k0 + k;
-                const C uk = H16 ? uin[H16 ? kk : 0][r] : ureg[kk][r];
+                C uk = ureg[kk][r];
+                if constexpr (H16 != 0) {
+                    uk = to<C>(urd[k][r]);
+                    if constexpr (PC != 0) uk *= (C)prd[k][r];
+                }
                 const C bk = helm ? to<C>(braw[k][r]) * bsc : (C)0;
                 const C wv = hs * wacc[kk][r] + h2 * bk * uk;
                 const TW ws = SUB ? (TW)(rraw[SUB ? k : 0][r] - to<TW>(wv)) : to<TW>(wv);
@@ -337,7 +367,13 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
                 if (a.pdot >= 0) dot[r] += (double)uk * (double)to<C>(ws);
             }
     }
-    if (a.pdot >= 0) {
+    if (a.pdot >= 0 && a.dots >= 0) {
+        // the columns' dots, for axw_dots_kernel
+        SEM_GLOBAL double* cd = gfieldw<double>(R, a.dots + comp) + (long long)ee * L2;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            if (live && ok[r]) cd[off[r]] = dot[r];
+    } else if (a.pdot >= 0) {
         // the columns' dots, summed in the order of the column kernel's threads
         double* cd = (double*)lds;
         block_sync_lds();
@@ -360,38 +396,78 @@ __global__ void __launch_bounds__(64 * epb_of(LX), 2) axw_kernel(Batch bt, AxLau
     }
 }
 
-template <int LX, typename TU, typename TG, typename C, int H16 = 0>
-static void axw_go(const Batch& b, const AxLaunch& a, hipStream_t s)
+// the partial sums of the column dots of an element block, in the order in
+// which axw_kernel adds them itself
+template <int LX>
+__global__ void __launch_bounds__((epb_of(LX) * LX * LX + 63) / 64 * 64) axw_dots_kernel(Batch bt, AxLaunch a)
 {
-    const dim3 grid(((b.eb[b.n] + 7) / 8) * 8 * a.ncomp), blk(64 * epb_of(LX));
+    constexpr int EPB = epb_of(LX), L2 = LX * LX, NW = (EPB * L2 + 63) / 64;
+    __shared__ double red[NW];
+    const int comp = blockIdx.y, g = blockIdx.x;
+    const int ri = find_req(bt.eb, bt.n, g);
+    const ReqDesc* R = bt.r[ri];
+    if (!gate_ok(R, a.gate < 0 ? -1 : a.gate + comp)) return;
+    const int blk = g - bt.eb[ri], t = threadIdx.x;
+    const long long q = (long long)blk * EPB * L2 + t;
+    const SEM_GLOBAL double* cd = gfield<double>(R, a.dots + comp);
+    const double s = wave_sum(t < EPB * L2 && q < (long long)R->E * L2 ? cd[q] : 0.0);
+    if ((t & 63) == 0) red[t >> 6] = s;
+    block_sync_lds();
+    if (t == 0) {
+        double v = 0.0;
+        for (int w = 0; w < NW; ++w) v += red[w];
+        gp(R->part)[(long long)(a.pdot + comp) * R->pstride + blk] = v;
+        if (blk == 0) gp(R->I)[I_PCNT + a.pdot + comp] = R->nb;
+    }
+}
+
+// Without the fused dot a wave is a workgroup of its own.  With it the
+// workgroups are the element blocks its partial sums are defined on, except
+// where these hold more than two waves and fill the chip: then the waves still
+// run alone and leave their column dots in the scratch field a.dots.  (At lx =
+// 10 a CU holds one workgroup of five fp64 waves, where eight fit: 20^3, three
+// components, 407 us against 330 with single waves.)
+template <int LX, typename TU, typename TG, typename C, int H16 = 0>
+static void axw_go(const Batch& b, const AxLaunch& a0, hipStream_t s)
+{
+    constexpr int EPB = epb_of(LX);
+    AxLaunch a = a0;
+    if (a.pdot >= 0 && (EPB <= 2 || b.el[b.n] < 2048)) a.dots = -1;
+    const bool blocks = a.pdot >= 0 && a.dots < 0;
+    const int n = blocks ? b.eb[b.n] : b.el[b.n];
+    const dim3 grid(((n + 7) / 8) * 8 * a.ncomp);
+#define AXW_GO(W, ...) hipLaunchKernelGGL((axw_kernel<LX, W, TU, TG, C, __VA_ARGS__>), grid, dim3(64 * W), 0, s, b, a)
     if constexpr (sizeof(TU) == 4) {
+        // the Arnoldi operator of an fp32 GMRES basis
         if (a.out64) {
-            if (a.precond >= 0 && a.tpc == P64)
-                hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 1, double, 0, H16>), grid, blk, 0, s, b, a);
-            else if (a.precond >= 0) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 2, double, 0, H16>), grid, blk, 0, s, b, a);
-            else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, double, 0, H16>), grid, blk, 0, s, b, a);
+            if (a.precond >= 0 && a.tpc == P64) AXW_GO(1, 1, double, 0, H16);
+            else if (a.precond >= 0) AXW_GO(1, 2, double, 0, H16);
+            else AXW_GO(1, 0, double, 0, H16);
             return;
         }
     }
     if constexpr (sizeof(TU) == 8) {
-        if (a.precond >= 0 && a.tpc == P64) {
-            hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 1, TU, 0, H16>), grid, blk, 0, s, b, a);
-            return;
-        }
-        if (a.precond >= 0) {
-            hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 2, TU, 0, H16>), grid, blk, 0, s, b, a);
-            return;
-        }
+        // the Arnoldi operator of an fp64 GMRES basis
+        if (a.precond >= 0 && a.tpc == P64) { AXW_GO(1, 1, TU, 0, H16); return; }
+        if (a.precond >= 0) { AXW_GO(1, 2, TU, 0, H16); return; }
     }
     if constexpr (sizeof(TU) == 8 && sizeof(TG) == 8 && sizeof(C) == 8 && H16 == 0) {
         if (a.sub >= 0) {
-            if (a.ncomp > 1) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 1, 0, 1>), grid, blk, 0, s, b, a);
-            else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 1>), grid, blk, 0, s, b, a);
+            if (a.ncomp > 1) AXW_GO(1, 0, TU, 1, 0, 1);
+            else AXW_GO(1, 0, TU, 1);
             return;
         }
     }
-    if (a.ncomp > 1) hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 0, H16, 1>), grid, blk, 0, s, b, a);
-    else hipLaunchKernelGGL((axw_kernel<LX, TU, TG, C, 0, TU, 0, H16>), grid, blk, 0, s, b, a);
+    if (blocks) {
+        if (a.ncomp > 1) AXW_GO(EPB, 0, TU, 0, H16, 1);
+        else AXW_GO(EPB, 0, TU, 0, H16);
+        return;
+    }
+    if (a.ncomp > 1) AXW_GO(1, 0, TU, 0, H16, 1);
+    else AXW_GO(1, 0, TU, 0, H16);
+    if (a.pdot >= 0)
+        hipLaunchKernelGGL(axw_dots_kernel<LX>, dim3(b.eb[b.n], a.ncomp), dim3((EPB * LX * LX + 63) / 64 * 64), 0, s, b, a);
+#undef AXW_GO
 }
 
 // the (vector, geometry, arithmetic) combinations of ax_lx (k_ax.hip)
@@ -413,20 +489,13 @@ template <int LX> static void axw_lx(const Batch& b, const AxLaunch& a, hipStrea
     else if (u == P32 && g == PBF && c == P32) axw_go<LX, float, __hip_bfloat16, float>(b, a, s);
     else if (u == P16 && g == P16 && c == P32) axw_go<LX, __half, __half, float>(b, a, s);
     else if (u == PBF && g == PBF && c == P32) axw_go<LX, __hip_bfloat16, __hip_bfloat16, float>(b, a, s);
-    else if (u == P32 && g == P16 && c == P16) axw_go<LX, float, __half, float, 1>(b, a, s);
-    else if (u == P16 && g == P16 && c == P16) axw_go<LX, __half, __half, float, 1>(b, a, s);
-    else if (u == P32 && g == PBF && c == PBF) axw_go<LX, float, __hip_bfloat16, float, 2>(b, a, s);
-    else if (u == PBF && g == PBF && c == PBF) axw_go<LX, __hip_bfloat16, __hip_bfloat16, float, 2>(b, a, s);
-}
-
-bool launch_ax_wide(const Batch& b, int lx, const AxLaunch& a, hipStream_t s)
-{
-    switch (lx) {
-    case 9: axw_lx<9>(b, a, s); return true;
-    case 10: axw_lx<10>(b, a, s); return true;
-    case 11: axw_lx<11>(b, a, s); return true;
-    case 12: axw_lx<12>(b, a, s); return true;
-    default: return false;
+    // 16-bit arithmetic: at lx = 11 the column kernel's LDS reads fall in
+    // different banks and it is faster (18^3: 57 us against 67)
+    if constexpr (LX != 11) {
+        if (u == P32 && g == P16 && c == P16) axw_go<LX, float, __half, float, 1>(b, a, s);
+        else if (u == P16 && g == P16 && c == P16) axw_go<LX, __half, __half, float, 1>(b, a, s);
+        else if (u == P32 && g == PBF && c == PBF) axw_go<LX, float, __hip_bfloat16, float, 2>(b, a, s);
+        else if (u == PBF && g == PBF && c == PBF) axw_go<LX, __hip_bfloat16, __hip_bfloat16, float, 2>(b, a, s);
     }
 }
 

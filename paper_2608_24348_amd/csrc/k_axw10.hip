@@ -1,0 +1,9 @@
+// The matrix-core Helmholtz/Poisson operator at lx = 10 (a source of its own per
+// order: the forms of one take minutes to compile).
+#include "k_axw.h"
+
+namespace semk {
+
+void launch_ax_wide10(const Batch& b, const AxLaunch& a, hipStream_t s) { axw_lx<10>(b, a, s); }
+
+}  // namespace semk

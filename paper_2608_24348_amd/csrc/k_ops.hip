@@ -76,6 +76,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, OpArrays i
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
+    SEM_GLOBAL double* out[3];
+    for (int f = 0; f < 3; ++f) out[f] = op_out(R, io, F_BN, f);
     C col[3][LX];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -108,7 +110,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, OpArrays i
                 C s = 0;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) s += col[c][k] * (m[0 * 3 + c] * dr + m[1 * 3 + c] * ds + m[2 * 3 + c] * dt);
-                op_out(R, io, F_BN, f)[ebase + p] = -(double)s;
+                out[f][ebase + p] = -(double)s;
             }
         }
         lds_handoff<OWave<LX>::v>();
@@ -136,6 +138,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
         b1 = S[S_BDF]; b2 = S[S_BDF + 1]; b3 = S[S_BDF + 2];
         idt = 1.0 / S[S_DT];
     }
+    SEM_GLOBAL double* out[3];
+    for (int c = 0; c < 3; ++c) out[c] = RHS ? gfieldw<double>(R, F_RHS + c) : op_out(R, io, dst, c);
     C col[LX];
 #pragma unroll
     for (int k = 0; k < LX; ++k) col[k] = (C)u[ebase + k * L2 + ij];
@@ -170,8 +174,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
                 C gc = ldm<TM, C>(M, ((long long)ee * 9 + 0 * 3 + c) * L3 + p, msc) * dr
                      + ldm<TM, C>(M, ((long long)ee * 9 + 1 * 3 + c) * L3 + p, msc) * ds
                      + ldm<TM, C>(M, ((long long)ee * 9 + 2 * 3 + c) * L3 + p, msc) * dt;
-                if constexpr (RHS) gfieldw<double>(R, F_RHS + c)[ebase + p] = ev[c] + (bv * idt) * hv[c] - (double)gc;
-                else op_out(R, io, dst, c)[ebase + p] = (double)gc;
+                if constexpr (RHS) out[c][ebase + p] = ev[c] + (bv * idt) * hv[c] - (double)gc;
+                else out[c][ebase + p] = (double)gc;
             }
         }
         lds_handoff<OWave<LX>::v>();
@@ -188,6 +192,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
+    const SEM_GLOBAL double* in[3];
+    for (int c = 0; c < 3; ++c) in[c] = op_in(R, io, src, c);
     C wacc[LX];
 #pragma unroll
     for (int k = 0; k < LX; ++k) wacc[k] = 0;
@@ -199,7 +205,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
         if (live) {
             C v[3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[c] = (C)op_in(R, io, src, c)[ebase + p];
+            for (int c = 0; c < 3; ++c) v[c] = (C)in[c][ebase + p];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll

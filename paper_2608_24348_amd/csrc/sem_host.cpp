@@ -705,9 +705,10 @@ void convection(const Batch& b, const sem_ctx* c, hipStream_t s, const OpArrays*
 }
 
 void ax(const Batch& b, int lx, int src, int dst, int ncomp, int hsel, double h1, double h2, int precond, int pdot,
-        int gate, int tu, int tg, int tc, hipStream_t s)
+        int gate, int tu, int tg, int tc, hipStream_t s, int dots = -1)
 {
     AxLaunch a;
+    a.dots = dots;
     a.src = src; a.src_vj = 0; a.dst = dst; a.ncomp = ncomp; a.hsel = hsel; a.h1 = h1; a.h2 = h2;
     a.precond = precond; a.tpc = P64; a.pdot = pdot; a.gate = gate; a.tu = tu; a.tg = tg; a.tc = tc; a.out64 = 0;
     a.u_raw = nullptr; a.w_raw = nullptr; a.sub = -1;
@@ -770,7 +771,8 @@ void pcg_iteration(const Batch& b, int lx, const Resolved& r, int tv, hipStream_
         ProfScope ps(SEM_PROF_AX_VEL, s);
         // alpha = rho / (p, w): the dot of a continuous p with dssum(w_L)
         // equals the plain local sum of p w_L, formed before the dssum
-        ax(b, lx, F_PP, F_PW, 3, S_H1, 0, 0, -1, R_A, I_VACT, tv, r.axv_g, r.axv_c, s);
+        // (z, formed anew by the update below, is free to hold the column dots)
+        ax(b, lx, F_PP, F_PW, 3, S_H1, 0, 0, -1, R_A, I_VACT, tv, r.axv_g, r.axv_c, s, F_PZ);
     }
     launch_dssum(b, F_PW, 3, tv, I_VACT, nullptr, s);
     fin(b, FIN_PCG_ALPHA, s);

@@ -305,6 +305,7 @@ struct AxLaunch {
     int precond;                // field id of the inverse diagonal applied to src on load, or -1
     int tpc;                    // PrecId of that diagonal (P64 or P32)
     int pdot;                   // reduction slot for sum(u*w) over local points, or -1
+    int dots = -1;              // field id of E*lx^2 doubles of scratch per component for that sum, or -1
     int gate;                   // I index checked per component (nonzero = run), or -1
     int tu, tg, tc;             // PrecId of vectors, geometry and arithmetic
     int out64;                  // nonzero: the output is fp64 whatever tu is (Arnoldi operator output)
@@ -325,8 +326,15 @@ void launch_ax(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
 // the matrix-core operator (lx = 8, fp32 arithmetic, 16-bit geometry, no Jacobi
 // scaling, residual form or fp64 output); false when it does not apply
 bool launch_ax_mfma(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
-// the matrix-core operator of lx = 9..12, every form; false for other orders
-bool launch_ax_wide(const Batch& b, int lx, const AxLaunch& a, hipStream_t s);
+// the column operator by order, and the matrix-core operator of lx = 10..12
+void launch_ax_col8(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_col9(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_col10(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_col11(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_col12(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_wide10(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_wide11(const Batch& b, const AxLaunch& a, hipStream_t s);
+void launch_ax_wide12(const Batch& b, const AxLaunch& a, hipStream_t s);
 // pslot >= 0: also the squared norm over unique nodes of each component c,
 // as per-workgroup partials in slot pslot + c (see gs_blocks for their count)
 void launch_dssum(const Batch& b, int field, int ncomp, int tprec, int gate, void* raw, hipStream_t s,
