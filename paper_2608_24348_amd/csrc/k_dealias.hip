@@ -5,12 +5,14 @@
 // with W = jac * (Gauss-Legendre weights).  The metric terms W dr_a/dx_c at
 // the fine points are computed once per mesh (dealias_geom_kernel) from the
 // interpolated coordinates.  Per element (one workgroup), the velocity and
-// its reference derivatives are taken to the fine points by three staged
-// one-dimensional contractions in LDS; the contravariant velocity
-// V_a = sum_c u_c W dr_a/dx_c stays in registers (each thread owns fixed
-// fine points), and the weighted integrand goes back to the GLL points by
-// the transposed contractions.
+// its reference derivatives are taken to the fine points by staged
+// one-dimensional contractions along whole lines; the contravariant velocity
+// V_a = sum_c u_c W dr_a/dx_c stays in registers (each thread owns a fine
+// line of the third index), and the weighted integrand goes back to the GLL
+// points by the transposed contractions.
 #include "k_common.h"
+
+#include <type_traits>
 
 namespace semk {
 
@@ -57,38 +59,6 @@ __device__ __forceinline__ void interp3(const C* A1, const C* A2, const C* A3, c
 #pragma unroll
         for (int c = 0; c < LX; ++c) s += A3[k * LX + c] * tB[(c * LXD + j) * LXD + i];
         out[idx] = s;
-    }
-    __syncthreads();
-}
-
-// transposed: out[(c LX + b) LX + a] = -sum_{k,j,i} A[i][a] A[j][b] A[k][c] in[(k LXD + j) LXD + i]
-template <int LX, typename C>
-__device__ __forceinline__ void back3_neg(const C* A, const C* in, C* tB, C* tA, SEM_GLOBAL double* out)
-{
-    constexpr int LXD = Dl<LX>::LXD, NT = Dl<LX>::NT;
-    const int t = threadIdx.x;
-    for (int idx = t; idx < LX * LXD * LXD; idx += NT) {
-        const int i = idx % LXD, r = idx / LXD, j = r % LXD, c = r / LXD;
-        C s = 0;
-#pragma unroll
-        for (int k = 0; k < LXD; ++k) s += A[k * LX + c] * in[(k * LXD + j) * LXD + i];
-        tB[idx] = s;
-    }
-    __syncthreads();
-    for (int idx = t; idx < LX * LX * LXD; idx += NT) {
-        const int i = idx % LXD, r = idx / LXD, b = r % LX, c = r / LX;
-        C s = 0;
-#pragma unroll
-        for (int j = 0; j < LXD; ++j) s += A[j * LX + b] * tB[(c * LXD + j) * LXD + i];
-        tA[idx] = s;
-    }
-    __syncthreads();
-    for (int idx = t; idx < LX * LX * LX; idx += NT) {
-        const int a = idx % LX, r = idx / LX;
-        C s = 0;
-#pragma unroll
-        for (int i = 0; i < LXD; ++i) s += A[i * LX + a] * tA[r * LXD + i];
-        out[idx] = -(double)s;
     }
     __syncthreads();
 }
@@ -218,658 +188,455 @@ template <typename TM> __device__ __forceinline__ int mfd_field() { return F_MFD
 template <> __device__ __forceinline__ int mfd_field<double>() { return F_MFD64; }
 template <> __device__ __forceinline__ int mfd_field<float>() { return F_MFD32; }
 
-// one fine-grid metric term in the arithmetic type (16-bit storage carries the element scale)
-template <typename TM, typename C> __device__ __forceinline__ C mload(const SEM_GLOBAL TM* p, C sc)
-{
-    if constexpr (sizeof(TM) == 2) return to<C>(ldg(p)) * sc;
-    else return (C)*p;
-}
+// scale of an element's 16-bit terms
 template <typename TM, typename C> __device__ __forceinline__ C mscale(const ReqDesc* R, int e)
 {
     if constexpr (sizeof(TM) == 2) return (C)gfield<float>(R, F_MFDSC)[e];
     else return (C)1;
 }
 
-// BN = dealiased -B (u . grad) u of the velocity field (F_U), fp64 output
-template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(Dl<LX>::NT) conv_dealias_kernel(Batch bt, OpArrays io)
-{
-    constexpr int LXD = Dl<LX>::LXD, N3 = Dl<LX>::N3, ND3 = Dl<LX>::ND3, NT = Dl<LX>::NT, NQ = Dl<LX>::NQ;
-    __shared__ C sI[LXD * LX], sID[LXD * LX];
-    __shared__ C su[3][N3];
-    __shared__ C F[ND3];
-    __shared__ C tA[Dl<LX>::NA], tB[Dl<LX>::NB];
-    const int g = blockIdx.x;
-    const int ri = find_req(bt.eb, bt.n, g);
-    const ReqDesc* R = bt.r[ri];
-    const int blk = g - bt.eb[ri];
-    const int t = threadIdx.x;
-    if constexpr (sizeof(C) == 8) {
-        const SEM_GLOBAL double* tab = gp(R->D64);
-        for (int q = t; q < LXD * LX; q += NT) {
-            sI[q] = (C)tab[dl_off64<LX>() + q];
-            sID[q] = (C)tab[dl_off64<LX>() + LXD * LX + q];
-        }
-    } else {
-        const SEM_GLOBAL float* tab = gp(R->D32);
-        for (int q = t; q < LXD * LX; q += NT) {
-            sI[q] = (C)tab[dl_off32<LX>() + q];
-            sID[q] = (C)tab[dl_off32<LX>() + LXD * LX + q];
-        }
-    }
-    const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
-    const SEM_GLOBAL double* U[3];
-    SEM_GLOBAL double* O[3];
-    for (int c = 0; c < 3; ++c) { U[c] = op_in(R, io, F_U, c); O[c] = op_out(R, io, F_BN, c); }
-    __syncthreads();
-    for (int el = 0; el < R->epb; ++el) {
-        const int e = blk * R->epb + el;
-        if (e >= R->E) break;
-        const long long eb = (long long)e * N3;
-        for (int p = t; p < N3; p += NT) {
-            su[0][p] = (C)U[0][eb + p];
-            su[1][p] = (C)U[1][eb + p];
-            su[2][p] = (C)U[2][eb + p];
-        }
-        __syncthreads();
-        const SEM_GLOBAL TM* me = MF + (long long)e * 9 * ND3;
-        const C msc = mscale<TM, C>(R, e);
-        // contravariant velocity V_a = sum_c u_c W dr_a/dx_c at this thread's fine points
-        C V[3][NQ];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int r = 0; r < NQ; ++r) V[a][r] = 0;
-        for (int c = 0; c < 3; ++c) {
-            interp3<LX, C>(sI, sI, sI, su[c], tA, tB, F);
-#pragma unroll
-            for (int r = 0; r < NQ; ++r) {
-                const int q = t + r * NT;
-                if (q < ND3) {
-                    const C uf = F[q];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) V[a][r] += uf * mload<TM, C>(me + (a * 3 + c) * ND3 + q, msc);
-                }
-            }
-            __syncthreads();
-        }
-        for (int f = 0; f < 3; ++f) {
-            C T[NQ];
-#pragma unroll
-            for (int r = 0; r < NQ; ++r) T[r] = 0;
-            for (int a = 0; a < 3; ++a) {
-                interp3<LX, C>(a == 0 ? sID : sI, a == 1 ? sID : sI, a == 2 ? sID : sI, su[f], tA, tB, F);
-#pragma unroll
-                for (int r = 0; r < NQ; ++r) {
-                    const int q = t + r * NT;
-                    if (q < ND3) T[r] += V[a][r] * F[q];
-                }
-                __syncthreads();
-            }
-#pragma unroll
-            for (int r = 0; r < NQ; ++r) {
-                const int q = t + r * NT;
-                if (q < ND3) F[q] = T[r];
-            }
-            __syncthreads();
-            back3_neg<LX, C>(sI, F, tB, tA, O[f] + eb);
-        }
-    }
-}
-
 // ------------------------------------------------------------------
-// Matrix-core form (LXD <= 16): every one-dimensional contraction is a small
-// dense product with the 1D matrix (I, ID or I^T) as one operand, done with
-// the 16x16x4 MFMA of the arithmetic type.  The matrix operands sit in
-// registers for the whole kernel (for these shapes the lane layout of the
-// A and B operands coincide: lane l holds row/column l % 16, k = l / 16), the
-// tensor operand is read from LDS once per stage, and the fine-grid products
-// stay in the accumulators, so LDS traffic drops from two reads per FMA to
-// about one read and one write per staged value.  Four waves share an
-// element; output tiles go round-robin over the waves.
-template <typename C> struct Mma;
-template <> struct Mma<float> {
-    typedef float V4 __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V4 mma(float a, float b, V4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    // accumulator entry r of a lane in row group g holds output row:
-    static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
-};
-template <> struct Mma<double> {
-    typedef double V4 __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V4 mma(double a, double b, V4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ int row(int g, int r) { return g + 4 * r; }
-};
-
-template <int LX> struct Dm {
-    static constexpr int LXD = (3 * LX + 1) / 2;
-    static constexpr int NL = LX * LX, NN = LXD * LXD, N3 = LX * LX * LX, ND3 = LXD * LXD * LXD;
-    static constexpr int KSX = (LX + 3) / 4, KSD = (LXD + 3) / 4;   // k-steps over coarse / fine indices
-    static constexpr int NLT = (NL + 15) / 16, NNT = (NN + 15) / 16;  // tiles over lines / fine planes
-    static constexpr int NW = 4, NT = 64 * NW;
-    static constexpr int JW = (NNT + NW - 1) / NW;                  // fine-plane tiles per wave
+// BN = dealiased -B (u . grad) u.  A thread takes a whole line through a
+// one-dimensional contraction, its inputs in registers and the matrix shared
+// by the wave, so a line of LX values becomes LXD for LX + LXD LDS accesses.
+// On the third index a thread owns the fine line (j', i') of the element: V_a,
+// the integrand T and the transposed contraction back to LX values never leave
+// its registers (15 LX LXD multiply-adds for 9 LX LDS reads).  Per element the
+// I I u_c stay in LDS for all three components (the third-index derivative
+// reads them again); the other two derivatives of a component pass through one
+// buffer.
+//   LDS: sIP [3][LX][NN], sB [LX][NN], sY [LX][LXD][LX|1] (then [NL][LXD|1]), for DPP I and ID
+// Every sum runs over its index in ascending order from zero with fused
+// multiply-adds; T adds its terms in the order K0, K1, K2.
+//
+// Bound by memory at LX <= 7 (the metric terms: 9 of 15 words at 3.4 times the
+// points) and by latency and the coefficients above: at LX = 12, fp64, without
+// coefficient reads 717, without metric loads 942, with neither nor u nor stores
+// 348 of 1233 us, VALU busy 24%, against 396 us for the bytes.  A tile form on
+// matrix cores pads lines of LX and LXD to 4 and 16, and passes V and T of a
+// component through LDS; lines pad only the last of their waves.  us a call,
+// tile form (LX <= 10) or one thread a point (11, 12) before, lines now:
+//   LX, elements     fp64          fp32          16-bit terms
+//    5, 32^3         665 -> 303    363 -> 186    377 -> 145
+//    7, 32 32 16     783 -> 459    390 -> 254    392 -> 234
+//    8, 32^3        1718 -> 1656   829 -> 742    782 -> 722
+//    9, 22^3        2396 -> 785    586 -> 415    535 -> 415
+//   10, 20^3        2302 -> 1125   577 -> 443    515 -> 420
+//   11, 18^3        3161 -> 1131  1954 -> 818   1960 -> 817
+//   12, 16^3        2388 -> 977   1298 -> 697   1291 -> 678
+template <int LX, typename C> struct Dn {
+    static constexpr int LXD = (3 * LX + 1) / 2, NL = LX * LX, NN = LXD * LXD, N3 = NL * LX, ND3 = NN * LXD;
+    static constexpr int LJ = LX | 1, LP = LXD | 1;   // odd row strides: lanes a row apart fall in different banks
     static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-    static constexpr int R1 = cmax(2 * NL * LXD, ND3);             // Y1 (P, Q) / T / Z2
-    static constexpr int R2 = 3 * LX * NN;                          // Y2 (3 kinds) / Z1
+    static constexpr int YS = cmax(LX * LXD * LJ, NL * LP);
+    static constexpr bool DPP = LX > 11;   // matrix entries by row broadcast (below)
+    static constexpr int TOTAL = 4 * LX * NN + YS + (DPP ? 2 * LXD * LX : 0);
+    static constexpr int NW = (NN + 63) / 64, NT = 64 * NW;
+    static_assert(TOTAL * (int)sizeof(C) <= 160 * 1024, "LDS of a workgroup");
+    // layers of metric terms in flight, the first of them (and u) loaded a stage
+    // ahead.  With V and T of 18 rows in fp64 the registers do not hold that:
+    // LX = 12, 1096 us with a ring of six and 977 with three on demand.
+    static constexpr bool TIGHT = DPP && sizeof(C) == 8;
+    static constexpr int RG = TIGHT ? 3 : LXD < 6 ? LXD : 6;
+    // workgroups a CU by LDS, at most three, and the waves per SIMD that go with
+    // them; more than two would spill V and T in fp64 (LX = 8: 2229 us at three,
+    // 1625 at two) and at LX = 12
+    static constexpr int WG = TOTAL * (int)sizeof(C) * 2 > 160 * 1024 ? 1 : TOTAL * (int)sizeof(C) * 3 > 160 * 1024 ? 2 : 3;
+    static constexpr int WPE0 = (WG * NW + 3) / 4, WPE = (sizeof(C) == 8 || DPP) && WPE0 > 2 ? 2 : WPE0;
 };
 
-template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__(Dm<LX>::NT) conv_dealias_mfma_kernel(Batch bt, OpArrays io)
+// The matrix entries of a line, two ways.
+// By row broadcast: row o sits in one register, entry a in lane a of every
+// 16-lane row of the wave (one LDS read for 3 rows), and a multiply-add takes it
+// with the row broadcast of its DPP operand; fp64 runs at 0.9 of its plain rate
+// so, fp32 at half.  By scalar registers (uniform loads): full rate, but a wave
+// waits for each batch, and all that the waves of an element read (404 KB at
+// LX = 12, fp64) comes through one scalar cache per two CUs.  us a call, fp64 /
+// fp32 / 16-bit terms:
+//          LX = 7         10               11               12
+//   scalar  442/245/228   1118/432/412     1152/803/801     1273/945/901
+//   DPP     472/279/284   1142/477/438     1231/899/895      967/670/650
+// so the line lies between 11 and 12.  A DPP operand must not have been written
+// by the two vector instructions before: the blocks begin with that wait,
+// whatever the compiler puts ahead of them.  Lanes of the row must be on.
+#define DL_OP64(d, c, x, n) "v_fmac_f64_dpp " d ", " c ", " x " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+#define DL_OP32(d, c, x, n) "v_fmac_f32_dpp " d ", " c ", " x " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+// three sums, one more input each: s_k += row_k[n] x
+#define DL_UP(OP, x, n) OP("%0", "%3", x, n) OP("%1", "%4", x, n) OP("%2", "%5", x, n)
+#define DL_UPS(OP, n0, n1, n2, n3, ...)                                                                                \
+    if constexpr (N == 4)                                                                                              \
+        asm("s_nop 1\n\t" DL_UP(OP, "%6", n0) DL_UP(OP, "%7", n1) DL_UP(OP, "%8", n2) DL_UP(OP, "%9", n3) __VA_ARGS__  \
+            : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3])); \
+    else if constexpr (N == 3)                                                                                         \
+        asm("s_nop 1\n\t" DL_UP(OP, "%6", n0) DL_UP(OP, "%7", n1) DL_UP(OP, "%8", n2) __VA_ARGS__                      \
+            : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(x[0]), "v"(x[1]), "v"(x[2])); \
+    else if constexpr (N == 2)                                                                                         \
+        asm("s_nop 1\n\t" DL_UP(OP, "%6", n0) DL_UP(OP, "%7", n1) __VA_ARGS__                                          \
+            : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(x[0]), "v"(x[1]));            \
+    else                                                                                                               \
+        asm("s_nop 1\n\t" DL_UP(OP, "%6", n0) __VA_ARGS__                                                              \
+            : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(x[0]));
+// s_k += sum over a = A .. A + N - 1 (ascending) of row_k[a] x[a - A], k = 0, 1, 2
+template <int A, int N, typename C> __device__ __forceinline__ void up_block(C (&s)[3], const C (&c)[3], const C* x)
 {
-    using D = Dm<LX>;
-    using M = Mma<C>;
-    typedef typename M::V4 V4;
-    constexpr int LXD = D::LXD, NL = D::NL, NN = D::NN, N3 = D::N3, ND3 = D::ND3;
-    constexpr int KSX = D::KSX, KSD = D::KSD, NLT = D::NLT, NNT = D::NNT, JW = D::JW;
-    static_assert(LXD <= 16, "one 16-row tile over the fine index");
-    __shared__ C sU[3 * N3];
-    __shared__ C R1[D::R1];
-    __shared__ C R2[D::R2];
-    const int gb = blockIdx.x;
-    const int ri = find_req(bt.eb, bt.n, gb);
-    const ReqDesc* R = bt.r[ri];
-    const int blk = gb - bt.eb[ri];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m = lane & 15, g = lane >> 4;
-    // 1D matrices in registers: fI/fD[s] = I/ID[m][4s+g] (forward stages), bI[s] = I[4s+g][m] (transposed stages)
-    C fI[KSX], fD[KSX], bI[KSD];
-    {
-        const int o = sizeof(C) == 8 ? dl_off64<LX>() : dl_off32<LX>();
-#pragma unroll
-        for (int s = 0; s < KSX; ++s) {
-            const int k = 4 * s + g;
-            const bool ok = m < LXD && k < LX;
-            if constexpr (sizeof(C) == 8) {
-                fI[s] = ok ? gp(R->D64)[o + m * LX + k] : 0.0;
-                fD[s] = ok ? gp(R->D64)[o + LXD * LX + m * LX + k] : 0.0;
-            } else {
-                fI[s] = ok ? gp(R->D32)[o + m * LX + k] : 0.0f;
-                fD[s] = ok ? gp(R->D32)[o + LXD * LX + m * LX + k] : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < KSD; ++s) {
-            const int k = 4 * s + g;
-            const bool ok = k < LXD && m < LX;
-            if constexpr (sizeof(C) == 8) bI[s] = ok ? gp(R->D64)[o + k * LX + m] : 0.0;
-            else bI[s] = ok ? gp(R->D32)[o + k * LX + m] : 0.0f;
-        }
+    if constexpr (sizeof(C) == 8) {
+        if constexpr (A == 0) { DL_UPS(DL_OP64, 0, 1, 2, 3) }
+        else if constexpr (A == 4) { DL_UPS(DL_OP64, 4, 5, 6, 7) }
+        else { DL_UPS(DL_OP64, 8, 9, 10, 11) }
+    } else {
+        if constexpr (A == 0) { DL_UPS(DL_OP32, 0, 1, 2, 3) }
+        else if constexpr (A == 4) { DL_UPS(DL_OP32, 4, 5, 6, 7) }
+        else { DL_UPS(DL_OP32, 8, 9, 10, 11) }
     }
-    const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
-    const SEM_GLOBAL double* U[3];
-    SEM_GLOBAL double* O[3];
-    for (int c = 0; c < 3; ++c) { U[c] = op_in(R, io, F_U, c); O[c] = op_out(R, io, F_BN, c); }
-    C* sY1 = R1;            // [2][NL][LXD]: P = I u, Q = ID u along the first index
-    C* sT = R1;             // [LXD][NN]: weighted integrand at the fine points
-    C* sZ2 = R1;            // [NL][LXD]
-    C* sY2 = R2;            // [3][LX][NN]
-    C* sZ1 = R2;            // [LX][NN]
+}
+// one row into N sums: y[a] += row[a] v
+#define DL_DN4(OP, c, v, n0, n1, n2, n3) OP("%0", c, v, n0) OP("%1", c, v, n1) OP("%2", c, v, n2) OP("%3", c, v, n3)
+#define DL_DN3(OP, c, v, n0, n1, n2, n3) OP("%0", c, v, n0) OP("%1", c, v, n1) OP("%2", c, v, n2)
+#define DL_DN2(OP, c, v, n0, n1, n2, n3) OP("%0", c, v, n0) OP("%1", c, v, n1)
+#define DL_DN1(OP, c, v, n0, n1, n2, n3) OP("%0", c, v, n0)
+#define DL_DNS(OP, n0, n1, n2, n3)                                                                                     \
+    if constexpr (N == 4)                                                                                              \
+        asm("s_nop 1\n\t" DL_DN4(OP, "%4", "%7", n0, n1, n2, n3) DL_DN4(OP, "%5", "%8", n0, n1, n2, n3)                \
+                DL_DN4(OP, "%6", "%9", n0, n1, n2, n3)                                                                 \
+            : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(v[0]), "v"(v[1]), "v"(v[2])); \
+    else if constexpr (N == 3)                                                                                         \
+        asm("s_nop 1\n\t" DL_DN3(OP, "%3", "%6", n0, n1, n2, n3) DL_DN3(OP, "%4", "%7", n0, n1, n2, n3)                \
+                DL_DN3(OP, "%5", "%8", n0, n1, n2, n3)                                                                 \
+            : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(v[0]), "v"(v[1]), "v"(v[2])); \
+    else if constexpr (N == 2)                                                                                         \
+        asm("s_nop 1\n\t" DL_DN2(OP, "%2", "%5", n0, n1, n2, n3) DL_DN2(OP, "%3", "%6", n0, n1, n2, n3)                \
+                DL_DN2(OP, "%4", "%7", n0, n1, n2, n3)                                                                 \
+            : "+v"(y[0]), "+v"(y[1]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(v[0]), "v"(v[1]), "v"(v[2]));             \
+    else                                                                                                               \
+        asm("s_nop 1\n\t" DL_DN1(OP, "%1", "%4", n0, n1, n2, n3) DL_DN1(OP, "%2", "%5", n0, n1, n2, n3)                \
+                DL_DN1(OP, "%3", "%6", n0, n1, n2, n3)                                                                 \
+            : "+v"(y[0]) : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(v[0]), "v"(v[1]), "v"(v[2]));
+// y[a - A] += row_0[a] v_0, then row_1[a] v_1, then row_2[a] v_2, a = A .. A + N - 1
+template <int A, int N, typename C> __device__ __forceinline__ void down_block(C* y, const C (&c)[3], const C (&v)[3])
+{
+    if constexpr (sizeof(C) == 8) {
+        if constexpr (A == 0) { DL_DNS(DL_OP64, 0, 1, 2, 3) }
+        else if constexpr (A == 4) { DL_DNS(DL_OP64, 4, 5, 6, 7) }
+        else { DL_DNS(DL_OP64, 8, 9, 10, 11) }
+    } else {
+        if constexpr (A == 0) { DL_DNS(DL_OP32, 0, 1, 2, 3) }
+        else if constexpr (A == 4) { DL_DNS(DL_OP32, 4, 5, 6, 7) }
+        else { DL_DNS(DL_OP32, 8, 9, 10, 11) }
+    }
+}
+template <int LX, typename C, int A = 0> __device__ __forceinline__ void up_row(C (&s)[3], const C (&c)[3], const C (&x)[LX])
+{
+    if constexpr (A < LX) {
+        up_block<A, (LX - A < 4 ? LX - A : 4), C>(s, c, x + A);
+        up_row<LX, C, A + 4>(s, c, x);
+    }
+}
+template <int LX, typename C, int A = 0> __device__ __forceinline__ void down_row(C (&y)[LX], const C (&c)[3], const C (&v)[3])
+{
+    if constexpr (A < LX) {
+        down_block<A, (LX - A < 4 ? LX - A : 4), C>(y + A, c, v);
+        down_row<LX, C, A + 4>(y, c, v);
+    }
+}
 
-    for (int el = 0; el < R->epb; ++el) {
-        const int e = blk * R->epb + el;
-        if (e >= R->E) break;
-        const long long eb = (long long)e * N3;
-        for (int p = t; p < 3 * N3; p += D::NT) {
-            const int c = p / N3;
-            sU[p] = (C)U[c][eb + (p - c * N3)];
+// A 1D matrix as line_up and line_down take it: by DPP this lane's entry of row
+// 0 in LDS; else the table in device memory, RB rows at a time (scalar loads
+// return in any order, so a wave waits for a whole batch; the address passes
+// through asm so that a batch is loaded where it is asked for).
+template <int LX, typename C, bool DPP> struct Mat;
+template <int LX, typename C> struct Mat<LX, C, true> {
+    const C* p;
+    static constexpr int RB = 3;
+};
+template <int LX, typename C> struct Mat<LX, C, false> {
+    unsigned lo, hi;
+    static constexpr int RB = sizeof(C) == 8 ? 3 : 6;
+    __device__ __forceinline__ void set(const void* p)
+    {
+        lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
+        hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)p >> 32));
+    }
+    __device__ __forceinline__ void load(int r0, int n, C (&c)[RB][LX])
+    {
+        lo = __builtin_amdgcn_readfirstlane(lo);
+        hi = __builtin_amdgcn_readfirstlane(hi);
+        asm volatile("" : "+s"(lo), "+s"(hi)::"memory");
+        typedef const __attribute__((address_space(4))) C* CP;
+        const CP q = (CP)((uintptr_t)lo | ((uintptr_t)hi << 32)) + r0 * LX;
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+#pragma unroll
+            for (int a = 0; a < LX; ++a) c[k][a] = r0 + k < n ? q[k * LX + a] : (C)0;
+    }
+};
+template <typename C> __device__ __forceinline__ void keep(C& v) { asm volatile("" : "+v"(v)); }
+
+// out(o, sum_a mat[o][a] x[a]) for the LXD rows o; every sum ascends in a from zero
+template <int LX, int LXD, bool DPP, typename C, typename F>
+__device__ __forceinline__ void line_up(Mat<LX, C, DPP> mat, const C (&x)[LX], F out)
+{
+    constexpr int RB = Mat<LX, C, DPP>::RB;
+#pragma unroll
+    for (int o = 0; o < LXD; o += RB) {
+        C s[RB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) s[k] = 0;
+        if constexpr (DPP) {
+            C c[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) c[k] = mat.p[(o + k < LXD ? o + k : o) * LX];
+            up_row<LX, C>(s, c, x);
+            if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2])::"memory");
+        } else {
+            C c[RB][LX];
+            mat.load(o, LXD, c);
+#pragma unroll
+            for (int a = 0; a < LX; ++a)
+#pragma unroll
+                for (int k = 0; k < RB; ++k) s[k] += c[k][a] * x[a];
+#pragma unroll
+            for (int k = 0; k < RB; ++k) keep(s[k]);
         }
-        block_sync_lds();
-        const SEM_GLOBAL TM* me = MF + (long long)e * 9 * ND3;
-        const C msc = mscale<TM, C>(R, e);
-
-        // ---- contravariant velocity V_a = sum_c u_c (W dr_a/dx_c) at this wave's fine points
-        V4 V[3][JW];
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int k = 0; k < RB; ++k)
+            if (o + k < LXD) out(o + k, s[k]);
+    }
+}
+// y[a] = sum_o mat[o][a] in(o), ascending in o from zero
+template <int LX, int LXD, bool DPP, typename C, typename F>
+__device__ __forceinline__ void line_down(Mat<LX, C, DPP> mat, F in, C (&y)[LX])
+{
+    constexpr int RB = Mat<LX, C, DPP>::RB;
 #pragma unroll
-            for (int j = 0; j < JW; ++j) V[a][j] = V4{0, 0, 0, 0};
-        for (int c = 0; c < 3; ++c) {
-            // first index: Y1[L][i'] = sum_a u[L][a] I[i'][a]
-            for (int lt = w; lt < NLT; lt += 4) {
-                V4 acc = {0, 0, 0, 0};
-                const int L = 16 * lt + m;
+    for (int a = 0; a < LX; ++a) y[a] = 0;
 #pragma unroll
-                for (int s = 0; s < KSX; ++s) {
-                    const int a = 4 * s + g;
-                    const C av = (L < NL && a < LX) ? sU[c * N3 + L * LX + a] : (C)0;
-                    acc = M::mma(av, fI[s], acc);
-                }
+    for (int o = 0; o < LXD; o += RB) {
+        if constexpr (DPP) {
+            C c[3], v[3];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int Lo = 16 * lt + M::row(g, r);
-                    if (Lo < NL && m < LXD) sY1[Lo * LXD + m] = acc[r];
-                }
+            for (int k = 0; k < 3; ++k) {
+                c[k] = mat.p[(o + k < LXD ? o + k : o) * LX];
+                v[k] = o + k < LXD ? in(o + k) : (C)0;
+                if (o + k >= LXD) c[k] = (C)0;   // past the last row nothing is added
             }
-            block_sync_lds();
-            // second index, per third-index plane cc: Y2[cc][j'][i'] = sum_b I[j'][b] Y1[cc LX + b][i']
-            for (int cc = w; cc < LX; cc += 4) {
-                V4 acc = {0, 0, 0, 0};
+            down_row<LX, C>(y, c, v);
+            if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(y[0])::"memory");
+        } else {
+            C c[RB][LX];
+            mat.load(o, LXD, c);
 #pragma unroll
-                for (int s = 0; s < KSX; ++s) {
-                    const int b = 4 * s + g;
-                    const C bv = (b < LX && m < LXD) ? sY1[(cc * LX + b) * LXD + m] : (C)0;
-                    acc = M::mma(fI[s], bv, acc);
-                }
+            for (int k = 0; k < RB; ++k) {
+                if (o + k >= LXD) continue;
+                const C v = in(o + k);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int jo = M::row(g, r);
-                    if (jo < LXD && m < LXD) sY2[cc * NN + jo * LXD + m] = acc[r];
-                }
+                for (int a = 0; a < LX; ++a) y[a] += c[k][a] * v;
             }
-            block_sync_lds();
-            // third index: u_c(k', n) = sum_cc I[k'][cc] Y2[cc][n], straight into V
 #pragma unroll
-            for (int j = 0; j < JW; ++j) {
-                const int tn = w + 4 * j;
-                if (tn < NNT) {
-                    const int n = 16 * tn + m;
-                    V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                    for (int s = 0; s < KSX; ++s) {
-                        const int cc = 4 * s + g;
-                        const C bv = (cc < LX && n < NN) ? sY2[cc * NN + n] : (C)0;
-                        acc = M::mma(fI[s], bv, acc);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int kk = M::row(g, r);
-                        if (n < NN && kk < LXD) {
-#pragma unroll
-                            for (int a = 0; a < 3; ++a) V[a][j][r] += acc[r] * mload<TM, C>(me + (a * 3 + c) * ND3 + kk * NN + n, msc);
-                        }
-                    }
-                }
-            }
-        }
-
-        // ---- per component: T = sum_a V_a d_a u_f at the fine points, tested back on the GLL points
-        for (int f = 0; f < 3; ++f) {
-            block_sync_lds();
-            // first index: P = I u_f, Q = ID u_f
-            for (int job = w; job < 2 * NLT; job += 4) {
-                const int which = job / NLT, lt = job - which * NLT;
-                const int L = 16 * lt + m;
-                V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSX; ++s) {
-                    const int a = 4 * s + g;
-                    const C av = (L < NL && a < LX) ? sU[f * N3 + L * LX + a] : (C)0;
-                    acc = M::mma(av, which ? fD[s] : fI[s], acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int Lo = 16 * lt + M::row(g, r);
-                    if (Lo < NL && m < LXD) sY1[which * NL * LXD + Lo * LXD + m] = acc[r];
-                }
-            }
-            block_sync_lds();
-            // second index: kind 0: I P (for d/dt), 1: ID P (d/ds), 2: I Q (d/dr)
-            for (int job = w; job < 3 * LX; job += 4) {
-                const int kind = job / LX, cc = job - kind * LX;
-                const C* src = sY1 + (kind == 2 ? NL * LXD : 0);
-                V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSX; ++s) {
-                    const int b = 4 * s + g;
-                    const C bv = (b < LX && m < LXD) ? src[(cc * LX + b) * LXD + m] : (C)0;
-                    acc = M::mma(kind == 1 ? fD[s] : fI[s], bv, acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int jo = M::row(g, r);
-                    if (jo < LXD && m < LXD) sY2[kind * LX * NN + cc * NN + jo * LXD + m] = acc[r];
-                }
-            }
-            block_sync_lds();
-            // third index: d/dt = ID (I P), d/ds = I (ID P), d/dr = I (I Q); T accumulated in registers
-#pragma unroll
-            for (int j = 0; j < JW; ++j) {
-                const int tn = w + 4 * j;
-                if (tn < NNT) {
-                    const int n = 16 * tn + m;
-                    V4 T = {0, 0, 0, 0};
-#pragma unroll
-                    for (int kind = 0; kind < 3; ++kind) {
-                        V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                        for (int s = 0; s < KSX; ++s) {
-                            const int cc = 4 * s + g;
-                            const C bv = (cc < LX && n < NN) ? sY2[kind * LX * NN + cc * NN + n] : (C)0;
-                            acc = M::mma(kind == 0 ? fD[s] : fI[s], bv, acc);
-                        }
-                        const int a = 2 - kind;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) T[r] += V[a][j][r] * acc[r];
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int kk = M::row(g, r);
-                        if (kk < LXD && n < NN) sT[kk * NN + n] = T[r];
-                    }
-                }
-            }
-            block_sync_lds();
-            // transposed third index: Z1[c][n] = sum_k' I[k'][c] T[k'][n]
-            for (int tn = w; tn < NNT; tn += 4) {
-                const int n = 16 * tn + m;
-                V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSD; ++s) {
-                    const int kk = 4 * s + g;
-                    const C bv = (kk < LXD && n < NN) ? sT[kk * NN + n] : (C)0;
-                    acc = M::mma(bI[s], bv, acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int c = M::row(g, r);
-                    if (c < LX && n < NN) sZ1[c * NN + n] = acc[r];
-                }
-            }
-            block_sync_lds();
-            // transposed second index, per plane c: Z2[c][b][i'] = sum_j' I[j'][b] Z1[c][j'][i']
-            for (int c = w; c < LX; c += 4) {
-                V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSD; ++s) {
-                    const int jj = 4 * s + g;
-                    const C bv = (jj < LXD && m < LXD) ? sZ1[c * NN + jj * LXD + m] : (C)0;
-                    acc = M::mma(bI[s], bv, acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int b = M::row(g, r);
-                    if (b < LX && m < LXD) sZ2[(c * LX + b) * LXD + m] = acc[r];
-                }
-            }
-            block_sync_lds();
-            // transposed first index: BN_f[L][a] = -sum_i' Z2[L][i'] I[i'][a]
-            for (int lt = w; lt < NLT; lt += 4) {
-                const int L = 16 * lt + m;
-                V4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSD; ++s) {
-                    const int ii = 4 * s + g;
-                    const C av = (L < NL && ii < LXD) ? sZ2[L * LXD + ii] : (C)0;
-                    acc = M::mma(av, bI[s], acc);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int Lo = 16 * lt + M::row(g, r);
-                    if (Lo < NL && m < LX) O[f][eb + Lo * LX + m] = -(double)acc[r];
-                }
-            }
+            for (int a = 0; a < LX; ++a) keep(y[a]);
         }
     }
 }
 
-// Single-pass matrix-core form: the three components go through every
-// stage together, so an element takes seven workgroup barriers.  About one
-// wave per 16-point tile of a fine-grid plane keeps the heaviest stage
-// (velocity, contravariant velocity and the three derivatives of each
-// component on the fine points) nearly balanced; the smaller stages
-// distribute their tiles round-robin.  Operand reads carry no bounds tests:
-// every 1D-matrix register is zero outside its index range, and every LDS
-// region is zero-filled at the start with a pad behind it, so out-of-range
-// lanes read finite values that either meet a zero matrix entry or land in
-// output rows/columns that are never stored.  Stores of partial tiles write
-// their unused lanes to a scratch slot instead of branching.
-template <int LX, typename C> struct Dv2 {
-    using D = Dm<LX>;
-    static constexpr int LXD = D::LXD, NL = D::NL, NN = D::NN, N3 = D::N3, ND3 = D::ND3;
-    // waves: one per fine tile, rounded down to a multiple of four so that
-    // two workgroups place evenly on the four SIMDs of a CU
-    static constexpr int NW = D::NNT <= 4 ? D::NNT : (D::NNT / 4) * 4, NT = 64 * NW;
-    static constexpr int PAD = 4 * NN + 64;
-    static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-    // region X: u (3 N3) + Y1 (6 NL LXD) | T (3 LXD^3) | Z2 (3 NL LXD); region Y: Y2 (9 LX NN) | Z1 (3 LX NN)
-    static constexpr int X = cmax(cmax(3 * N3 + 6 * NL * LXD, 3 * ND3), 3 * NL * LXD) + PAD;
-    static constexpr int Y = 9 * LX * NN + PAD;
-    static constexpr int DUMMY = X + Y;          // 64 scratch slots for unused lanes of partial tiles
-    static constexpr int TOTAL = X + Y + 64;
-    static constexpr bool fits = TOTAL * (int)sizeof(C) <= 160 * 1024 && LXD <= 16 && NW <= 16;
-    // workgroups per CU that the LDS allows (at most 2), and the waves per SIMD
-    // the register allocation must leave room for so that they are co-resident
-    // (a workgroup's waves go round-robin over the four SIMDs, so a SIMD may
-    // hold ceil(NW/4) waves of each)
-    static constexpr int WG = TOTAL * (int)sizeof(C) * 2 <= 160 * 1024 ? 2 : 1;
-    static constexpr int WPE = WG * ((NW + 3) / 4);
-    static constexpr int NUP = (N3 + NT - 1) / NT;   // velocity points per thread
-};
-
-template <int LX, typename TM, typename C>
-__global__ void __launch_bounds__((Dv2<LX, C>::NT), (Dv2<LX, C>::WPE)) conv_dealias_v2_kernel(Batch bt, OpArrays io)
+// K0, K1, K2: the order in which T adds V_r d_r u (0), V_s d_s u (1), V_t d_t u (2)
+template <int LX, typename TM, typename C, int K0, int K1, int K2>
+__global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealias_line_kernel(Batch bt, OpArrays io)
 {
-    using D = Dm<LX>;
-    using Q = Dv2<LX, C>;
-    using M = Mma<C>;
-    typedef typename M::V4 V4;
-    constexpr int LXD = D::LXD, NL = D::NL, NN = D::NN, N3 = D::N3, ND3 = D::ND3;
-    constexpr int KSX = D::KSX, KSD = D::KSD, NLT = D::NLT, NNT = D::NNT, NW = Q::NW;
-    static_assert(Q::fits, "LDS footprint");
-    __shared__ C lds[Q::TOTAL];
-    C* const sU = lds;                       // [3][N3]
-    C* const sY1 = lds + 3 * N3;             // [3][2][NL][LXD]: P = I u, Q = ID u along the first index
-    C* const sT = lds;                       // [3][LXD^3]
-    C* const sZ2 = lds;                      // [3][NL][LXD]
-    C* const sY2 = lds + Q::X;               // [3][3][LX][NN]: I P, ID P, I Q along the second index
-    C* const sZ1 = lds + Q::X;               // [3][LX][NN]
+    using D = Dn<LX, C>;
+    constexpr int LXD = D::LXD, NL = D::NL, NN = D::NN, N3 = D::N3, ND3 = D::ND3, LJ = D::LJ, LP = D::LP;
+    __shared__ C lds[D::TOTAL];
+    C* const sIP = lds;
+    C* const sB = lds + 3 * LX * NN;
+    C* const sY = sB + LX * NN;
     const int gb = blockIdx.x;
-    const int ri = find_req(bt.eb, bt.n, gb);
+    const int ri = find_req(bt.el, bt.n, gb);
     const ReqDesc* R = bt.r[ri];
-    const int blk = gb - bt.eb[ri];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m = lane & 15, g = lane >> 4;
-    const int dummy = Q::DUMMY + lane;
-    for (int p = t; p < Q::TOTAL; p += Q::NT) lds[p] = (C)0;
-    C fI[KSX], fD[KSX], bI[KSD];
-    {
-        const int o = sizeof(C) == 8 ? dl_off64<LX>() : dl_off32<LX>();
-#pragma unroll
-        for (int s = 0; s < KSX; ++s) {
-            const int k = 4 * s + g;
-            const bool ok = m < LXD && k < LX;
-            if constexpr (sizeof(C) == 8) {
-                fI[s] = ok ? gp(R->D64)[o + m * LX + k] : 0.0;
-                fD[s] = ok ? gp(R->D64)[o + LXD * LX + m * LX + k] : 0.0;
-            } else {
-                fI[s] = ok ? gp(R->D32)[o + m * LX + k] : 0.0f;
-                fD[s] = ok ? gp(R->D32)[o + LXD * LX + m * LX + k] : 0.0f;
-            }
+    if (!gate_ok(R, bt.gate)) return;
+    const int e = gb - bt.el[ri];
+    const int t = threadIdx.x;
+    constexpr bool DPP = D::DPP;
+    Mat<LX, C, DPP> mI, mD;
+    if constexpr (DPP) {
+        C* const sM = sY + D::YS;
+        for (int q = t; q < 2 * LXD * LX; q += D::NT) {
+            if constexpr (sizeof(C) == 8) sM[q] = gp(R->D64)[dl_off64<LX>() + q];
+            else sM[q] = gp(R->D32)[dl_off32<LX>() + q];
         }
-#pragma unroll
-        for (int s = 0; s < KSD; ++s) {
-            const int k = 4 * s + g;
-            const bool ok = k < LXD && m < LX;
-            if constexpr (sizeof(C) == 8) bI[s] = ok ? gp(R->D64)[o + k * LX + m] : 0.0;
-            else bI[s] = ok ? gp(R->D32)[o + k * LX + m] : 0.0f;
-        }
+        mI.p = sM + ((t & 15) < LX ? t & 15 : LX - 1);
+        mD.p = mI.p + LXD * LX;
+        block_sync_lds();
+    } else {
+        const C* tab;
+        if constexpr (sizeof(C) == 8) tab = R->D64 + dl_off64<LX>();
+        else tab = R->D32 + dl_off32<LX>();
+        mI.set(tab);
+        mD.set(tab + LXD * LX);
     }
-    const SEM_GLOBAL TM* MF = gfield<TM>(R, mfd_field<TM>());
-    const SEM_GLOBAL double* U0 = op_in(R, io, F_U, 0);
-    const SEM_GLOBAL double* U1 = op_in(R, io, F_U, 1);
-    const SEM_GLOBAL double* U2 = op_in(R, io, F_U, 2);
-    SEM_GLOBAL double* O0 = op_out(R, io, F_BN, 0);
-    SEM_GLOBAL double* O1 = op_out(R, io, F_BN, 1);
-    SEM_GLOBAL double* O2 = op_out(R, io, F_BN, 2);
 
-    // the velocity of the next element is loaded while the current one is processed
-    constexpr int NUP = Q::NUP;
-    double un[3][NUP];
-    auto load_u = [&](int e) {
-        const long long eb = (long long)e * N3;
+    // A wave whose first line is in range runs with every lane on, as the row
+    // broadcasts need: lanes past the last line repeat it, and write what its
+    // owner writes.
+    const int t0 = __builtin_amdgcn_readfirstlane(t);
+    auto lane_of = [&](int q0, int n) { return q0 + (t - t0) < n ? q0 + (t - t0) : n - 1; };
+    const int tl = lane_of(t0, NL);
+
+    // first index: sY[k][i'][j] = sum_a mat[i'][a] u_c[k][j][a], line t = (k, j)
+    double xu[LX];
+    auto load_u = [&](int c) {
+        if (t0 < NL) {
+            const SEM_GLOBAL double* u = op_in(R, io, F_U, c) + (long long)e * N3 + tl * LX;
 #pragma unroll
-        for (int q = 0; q < NUP; ++q) {
-            const int p = t + q * Q::NT;
-            const int pc = p < N3 ? p : N3 - 1;
-            un[0][q] = U0[eb + pc];
-            un[1][q] = U1[eb + pc];
-            un[2][q] = U2[eb + pc];
+            for (int a = 0; a < LX; ++a) xu[a] = u[a];
         }
     };
-    const int e0 = blk * R->epb;
-    if (e0 < R->E) load_u(e0);
-    for (int el = 0; el < R->epb; ++el) {
-        const int e = blk * R->epb + el;
-        if (e >= R->E) break;
-        const long long eb = (long long)e * N3;
-        block_sync_lds();  // the previous element's last stage has read region X
+    auto first = [&](const Mat<LX, C, DPP>& mat, int c) {
+        if (D::TIGHT) load_u(c);
+        if (t0 < NL) {
+            C x[LX];
 #pragma unroll
-        for (int q = 0; q < NUP; ++q) {
-            const int p = t + q * Q::NT;
-            if (p < N3) {
-                sU[p] = (C)un[0][q];
-                sU[N3 + p] = (C)un[1][q];
-                sU[2 * N3 + p] = (C)un[2][q];
-            }
+            for (int a = 0; a < LX; ++a) x[a] = (C)xu[a];
+            C* y = sY + (tl / LX) * LXD * LJ + tl % LX;
+            line_up<LX, LXD, DPP>(mat, x, [&](int o, C v) { y[o * LJ] = v; });
         }
-        if (el + 1 < R->epb && e + 1 < R->E) load_u(e + 1);
-        block_sync_lds();
-        // S1, first index: Y1[c][mat][L][i'] = sum_a u_c[L][a] mat[i'][a]
-        for (int job = w; job < 6 * NLT; job += NW) {
-            const int cm = job / NLT, lt = job - cm * NLT;
-            const int c = cm >> 1, mat = cm & 1;
-            const C* src = sU + c * N3 + (16 * lt + m) * LX + g;
-            V4 acc = {0, 0, 0, 0};
+    };
+    // second index: dst[k][j'][i'] = sum_b mat[j'][b] sY[k][i'][b], line q = (k, i')
+    auto second = [&](const Mat<LX, C, DPP>& mat, C* dst) {
+        for (int q0 = t0; q0 < LX * LXD; q0 += D::NT) {
+            const int q = lane_of(q0, LX * LXD);
+            const C* y = sY + q * LJ;
+            C x[LX];
 #pragma unroll
-            for (int s = 0; s < KSX; ++s) acc = M::mma(src[4 * s], mat ? fD[s] : fI[s], acc);
-            C* dst = sY1 + cm * NL * LXD;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int L = 16 * lt + M::row(g, r);
-                lds[(L < NL && m < LXD) ? (int)(dst - lds) + L * LXD + m : dummy] = acc[r];
-            }
+            for (int b = 0; b < LX; ++b) x[b] = y[b];
+            C* o2 = dst + (q / LXD) * NN + q % LXD;
+            line_up<LX, LXD, DPP>(mat, x, [&](int o, C v) { o2[o * LXD] = v; });
         }
-        block_sync_lds();
-        // S2, second index per plane cc: kind 0 I P, 1 ID P, 2 I Q
-        for (int job = w; job < 9 * LX; job += NW) {
-            const int ck = job / LX, cc = job - ck * LX;
-            const int c = ck / 3, kind = ck - 3 * c;
-            const C* src = sY1 + (2 * c + (kind == 2)) * NL * LXD + (cc * LX + g) * LXD + m;
-            V4 acc = {0, 0, 0, 0};
+    };
+    const bool fine = t < NN;
+    const int n = fine ? t : NN - 1;   // lanes past the plane repeat its last line and store nothing
+    auto third_in = [&](const C* src, C (&x)[LX]) {
 #pragma unroll
-            for (int s = 0; s < KSX; ++s) acc = M::mma(kind == 1 ? fD[s] : fI[s], src[4 * s * LXD], acc);
-            const int base = (int)(sY2 - lds) + ck * LX * NN + cc * NN;
+        for (int k = 0; k < LX; ++k) x[k] = src[k * NN + n];
+    };
+
+    // metric term (ac, k') of the line; 16-bit terms of lx <= 10 are lane-ordered
+    const SEM_GLOBAL TM* me = gfield<TM>(R, mfd_field<TM>());
+    constexpr bool LANE = sizeof(TM) == 2 && dl16_lane(LX);
+    constexpr int NG = (LXD + 3) / 4;
+    if constexpr (LANE) me += (long long)e * dl16_per_elem(LX) + (long long)(n >> 4) * 9 * NG * 64 + (n & 15) * 4;
+    else me += (long long)e * 9 * ND3 + n;
+    // row g = c LR + k' of the terms (a, c), a = 0..2: a ring of RG rows in flight,
+    // loaded GR rows at a time (lane-ordered terms: four, in one load)
+    constexpr int GR = LANE ? 4 : 1, LR = LANE ? 4 * NG : LXD;
+    constexpr int RG = D::RG < GR ? GR : D::RG / GR * GR;
+    TM mr[RG][3];
+    auto load_m = [&](int g) {
+        const int c = g / LR, k = g % LR;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int jo = M::row(g, r);
-                lds[(jo < LXD && m < LXD) ? base + jo * LXD + m : dummy] = acc[r];
-            }
-        }
-        block_sync_lds();
-        // S3, third index, one fine tile per wave: u_c, V_a = sum_c u_c W dr_a/dx_c,
-        // then T_f = V_r d_r u_f + V_s d_s u_f + V_t d_t u_f
-        const SEM_GLOBAL TM* me = MF + (long long)e * 9 * ND3;
-        const C msc = mscale<TM, C>(R, e);
-        for (int tn = w; tn < NNT; tn += NW) {
-            const int n = 16 * tn + m;
-            int qoff[4];
+        for (int a = 0; a < 3; ++a) {
+            const int ac = a * 3 + c;
+            if constexpr (LANE) {
+                typedef unsigned short U4 __attribute__((ext_vector_type(4)));
+                const U4 q = *reinterpret_cast<const SEM_GLOBAL U4*>(me + (ac * NG + (k >> 2)) * 64);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int kk = M::row(g, r);
-                qoff[r] = (kk < LXD ? kk : LXD - 1) * NN + (n < NN ? n : NN - 1);
-            }
-            C mf[9][4];
-            if constexpr (sizeof(TM) == 2) {
-                // lane-ordered 16-bit terms: four rows of one term in one 8-byte load
-                static_assert(dl16_lane(LX), "lane-ordered 16-bit metric layout");
-                constexpr int NG = (LXD + 3) / 4;
-                const SEM_GLOBAL TM* m16 = MF + (long long)e * dl16_per_elem(LX) + (long long)tn * 9 * NG * 64;
-                // row groups past the fine grid (g >= NG) read the last group
-                // instead: unconditional loads, and those rows are never stored
-                const int gg = g < NG ? g : NG - 1;
-                unsigned long long raw[9];
-#pragma unroll
-                for (int ac = 0; ac < 9; ++ac)
-                    raw[ac] = *(const SEM_GLOBAL unsigned long long*)(m16 + (ac * NG + gg) * 64 + m * 4);
-#pragma unroll
-                for (int ac = 0; ac < 9; ++ac)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const unsigned short hb = (unsigned short)((raw[ac] >> (16 * r)) & 0xffff);
-                        TM hv;
-                        __builtin_memcpy(&hv, &hb, 2);
-                        mf[ac][r] = to<C>(hv) * msc;
-                    }
+                for (int j = 0; j < 4; ++j) mr[(g + j) % RG][a] = __builtin_bit_cast(TM, (unsigned short)q[j]);
             } else {
-#pragma unroll
-                for (int ac = 0; ac < 9; ++ac)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) mf[ac][r] = mload<TM, C>(me + ac * ND3 + qoff[r], msc);
+                mr[g % RG][a] = ldg(me + ac * ND3 + k * NN);
             }
-            const C* y2 = sY2 + g * NN + n;
-            V4 V[3];
+        }
+    };
+
+    // ---- I I u_c of the three components, then V_a on the thread's fine line
+    if constexpr (!D::TIGHT) load_u(0);
+    auto start_m = [&]() {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) V[a] = V4{0, 0, 0, 0};
+        for (int g = 0; g < RG; g += GR) load_m(g);
+    };
+    if constexpr (!D::TIGHT) start_m();
+    for (int c = 0; c < 3; ++c) {
+        first(mI, c);
+        if constexpr (!D::TIGHT) load_u(c < 2 ? c + 1 : 0);
+        block_sync_lds();
+        second(mI, sIP + c * LX * NN);
+        block_sync_lds();
+    }
+    if constexpr (D::TIGHT) start_m();
+    const C msc = mscale<TM, C>(R, e);
+    C V[3][LXD];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                V4 uc = {0, 0, 0, 0};
+    for (int c = 0; c < 3; ++c) {
+        C x[LX];
+        third_in(sIP + c * LX * NN, x);
+        line_up<LX, LXD, DPP>(mI, x, [&](int k, C v) {
+            const int g = c * LR + k;
 #pragma unroll
-                for (int s = 0; s < KSX; ++s) uc = M::mma(fI[s], y2[(3 * c) * LX * NN + 4 * s * NN], uc);
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) V[a][r] += uc[r] * mf[a * 3 + c][r];
+            for (int a = 0; a < 3; ++a) {
+                C mv = to<C>(mr[g % RG][a]);
+                if constexpr (sizeof(TM) == 2) mv *= msc;
+                V[a][k] = fma(v, mv, c == 0 ? (C)0 : V[a][k]);
             }
-#pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                V4 dt = {0, 0, 0, 0}, ds = {0, 0, 0, 0}, dr = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < KSX; ++s) {
-                    dt = M::mma(fD[s], y2[(3 * f + 0) * LX * NN + 4 * s * NN], dt);
-                    ds = M::mma(fI[s], y2[(3 * f + 1) * LX * NN + 4 * s * NN], ds);
-                    dr = M::mma(fI[s], y2[(3 * f + 2) * LX * NN + 4 * s * NN], dr);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int kk = M::row(g, r);
-                    const C T = V[0][r] * dr[r] + V[1][r] * ds[r] + V[2][r] * dt[r];
-                    lds[(kk < LXD && n < NN) ? (int)(sT - lds) + f * ND3 + kk * NN + n : dummy] = T;
-                }
+            // the row just read frees its slot
+            if (k % GR == GR - 1 || k == LXD - 1) {
+                const int g0 = g - k % GR;
+                if (g0 + RG < 3 * LR) load_m(g0 + RG);
             }
+        });
+    }
+
+    // ---- per component: T = sum_a V_a d_a u_f, back through the three indices
+    for (int f = 0; f < 3; ++f) {
+        C T[LXD];
+#pragma unroll
+        for (int k = 0; k < LXD; ++k) T[k] = 0;
+        auto add = [&](auto kind_) {
+            constexpr int kind = decltype(kind_)::value;
+            const C* src = sIP + f * LX * NN;
+            if constexpr (kind < 2) {
+                first(kind == 0 ? mD : mI, f);
+                block_sync_lds();
+                second(kind == 0 ? mI : mD, sB);
+                block_sync_lds();
+                src = sB;
+            }
+            C x[LX];
+            third_in(src, x);
+            line_up<LX, LXD, DPP>(kind == 2 ? mD : mI, x, [&](int k, C v) { T[k] = fma(V[kind][k], v, T[k]); });
+            // (the next write to sB or sIP comes after another barrier: every
+            // kind that uses sB passes the one behind its first index)
+        };
+        add(std::integral_constant<int, K0>());
+        add(std::integral_constant<int, K1>());
+        add(std::integral_constant<int, K2>());
+        if (!D::TIGHT && f < 2) load_u(f + 1);
+        C z[LX];
+        line_down<LX, LXD, DPP>(mI, [&](int k) { return T[k]; }, z);
+        block_sync_lds();   // sB has been read
+        if (fine) {
+#pragma unroll
+            for (int c = 0; c < LX; ++c) sB[c * NN + n] = z[c];
         }
         block_sync_lds();
-        // B1, transposed third index: Z1[f][c][n] = sum_k' I[k'][c] T_f[k'][n]
-        for (int job = w; job < 3 * NNT; job += NW) {
-            const int f = job / NNT, tn = job - f * NNT;
-            const int n = 16 * tn + m;
-            const C* src = sT + f * ND3 + g * NN + n;
-            V4 acc = {0, 0, 0, 0};
+        // transposed second index: sY[(c, b)][i'] = sum_j' I[j'][b] sB[c][j'][i'], line (c, i')
+        for (int q0 = t0; q0 < LX * LXD; q0 += D::NT) {
+            const int q = lane_of(q0, LX * LXD);
+            const C* src = sB + (q / LXD) * NN + q % LXD;
+            C y[LX];
+            line_down<LX, LXD, DPP>(mI, [&](int o) { return src[o * LXD]; }, y);
+            C* dst = sY + (q / LXD) * LX * LP + q % LXD;
 #pragma unroll
-            for (int s = 0; s < KSD; ++s) acc = M::mma(bI[s], src[4 * s * NN], acc);
-            const int base = (int)(sZ1 - lds) + f * LX * NN;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int c = M::row(g, r);
-                lds[(c < LX && n < NN) ? base + c * NN + n : dummy] = acc[r];
-            }
+            for (int b = 0; b < LX; ++b) dst[b * LP] = y[b];
         }
         block_sync_lds();
-        // B2, transposed second index per plane c: Z2[f][c LX + b][i'] = sum_j' I[j'][b] Z1[f][c][j'][i']
-        for (int job = w; job < 3 * LX; job += NW) {
-            const int f = job / LX, c = job - f * LX;
-            const C* src = sZ1 + f * LX * NN + c * NN + g * LXD + m;
-            V4 acc = {0, 0, 0, 0};
+        // transposed first index: BN_f[c][b][a] = -sum_i' I[i'][a] sY[(c, b)][i'], line t = (c, b)
+        if (t0 < NL) {
+            const C* src = sY + tl * LP;
+            C y[LX];
+            line_down<LX, LXD, DPP>(mI, [&](int o) { return src[o]; }, y);
+            SEM_GLOBAL double* o = op_out(R, io, F_BN, f) + (long long)e * N3 + t * LX;
+            if (t < NL) {
 #pragma unroll
-            for (int s = 0; s < KSD; ++s) acc = M::mma(bI[s], src[4 * s * LXD], acc);
-            const int base = (int)(sZ2 - lds) + f * NL * LXD + c * LX * LXD;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int b = M::row(g, r);
-                lds[(b < LX && m < LXD) ? base + b * LXD + m : dummy] = acc[r];
+                for (int a = 0; a < LX; ++a) o[a] = -(double)y[a];
             }
         }
-        block_sync_lds();
-        // B3, transposed first index: BN_f[L][a] = -sum_i' Z2[f][L][i'] I[i'][a]
-        for (int job = w; job < 3 * NLT; job += NW) {
-            const int f = job / NLT, lt = job - f * NLT;
-            const C* src = sZ2 + f * NL * LXD + (16 * lt + m) * LXD + g;
-            V4 acc = {0, 0, 0, 0};
-#pragma unroll
-            for (int s = 0; s < KSD; ++s) acc = M::mma(src[4 * s], bI[s], acc);
-            SEM_GLOBAL double* O = f == 0 ? O0 : f == 1 ? O1 : O2;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int L = 16 * lt + M::row(g, r);
-                if (L < NL && m < LX) O[eb + L * LX + m] = -(double)acc[r];
-            }
-        }
+        block_sync_lds();   // sY has been read
     }
 }
 
@@ -902,15 +669,14 @@ void launch_conv_dealias(const Batch& b, int lx, int tm, int tc, hipStream_t s, 
 {
     const OpArrays io = arrays ? *arrays : OpArrays{};
     if (b.eb[b.n] == 0) return;
-    // matrix-core form while the fine grid fits one 16-row tile (lx <= 10)
+    // the order of T's three terms: a step's fields answer to its last bit, so
+    // each order and precision adds them as it always has
 #define GO3(L, TM, C)                                                                                                  \
     do {                                                                                                               \
-        if constexpr (Dv2<L, C>::fits)                                                                                 \
-            hipLaunchKernelGGL((conv_dealias_v2_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3((Dv2<L, C>::NT)), 0, s, b, io);  \
-        else if constexpr ((3 * L + 1) / 2 <= 16)                                                                      \
-            hipLaunchKernelGGL((conv_dealias_mfma_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dm<L>::NT), 0, s, b, io);      \
-        else                                                                                                           \
-            hipLaunchKernelGGL((conv_dealias_kernel<L, TM, C>), dim3(b.eb[b.n]), dim3(Dl<L>::NT), 0, s, b, io);           \
+        constexpr bool swap = L <= 8 || (L <= 10 && sizeof(C) == 4), back = !swap && L <= 10;                          \
+        hipLaunchKernelGGL((conv_dealias_line_kernel<L, TM, C, (swap ? 1 : back ? 2 : 0), (swap ? 0 : 1),              \
+                                                     (swap || !back ? 2 : 0)>),                                        \
+                           dim3(b.el[b.n]), dim3((Dn<L, C>::NT)), 0, s, b, io);                                        \
     } while (0)
     if (tm == P64) {
 #define GO(L) GO3(L, double, double)
