@@ -10,7 +10,7 @@
 // V_a = sum_c u_c W dr_a/dx_c stays in registers (each thread owns a fine
 // line of the third index), and the weighted integrand goes back to the GLL
 // points by the transposed contractions.
-#include "k_common.h"
+#include "k_lines.h"
 
 #include <type_traits>
 
@@ -339,101 +339,50 @@ template <int LX, typename C, int A = 0> __device__ __forceinline__ void down_ro
     }
 }
 
-// A 1D matrix as line_up and line_down take it: by DPP this lane's entry of row
-// 0 in LDS; else the table in device memory, RB rows at a time (scalar loads
-// return in any order, so a wave waits for a whole batch; the address passes
-// through asm so that a batch is loaded where it is asked for).
-template <int LX, typename C, bool DPP> struct Mat;
-template <int LX, typename C> struct Mat<LX, C, true> {
-    const C* p;
-    static constexpr int RB = 3;
-};
-template <int LX, typename C> struct Mat<LX, C, false> {
-    unsigned lo, hi;
-    static constexpr int RB = sizeof(C) == 8 ? 3 : 6;
-    __device__ __forceinline__ void set(const void* p)
-    {
-        lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
-        hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)p >> 32));
-    }
-    __device__ __forceinline__ void load(int r0, int n, C (&c)[RB][LX])
-    {
-        lo = __builtin_amdgcn_readfirstlane(lo);
-        hi = __builtin_amdgcn_readfirstlane(hi);
-        asm volatile("" : "+s"(lo), "+s"(hi)::"memory");
-        typedef const __attribute__((address_space(4))) C* CP;
-        const CP q = (CP)((uintptr_t)lo | ((uintptr_t)hi << 32)) + r0 * LX;
-#pragma unroll
-        for (int k = 0; k < RB; ++k)
-#pragma unroll
-            for (int a = 0; a < LX; ++a) c[k][a] = r0 + k < n ? q[k * LX + a] : (C)0;
-    }
-};
-template <typename C> __device__ __forceinline__ void keep(C& v) { asm volatile("" : "+v"(v)); }
+// a 1D matrix as line_up and line_down take it: by DPP this lane's entry of row 0 in LDS
+template <typename C> struct LaneMat { const C* p; };
+template <int LX, typename C, bool DPP> using Mat = std::conditional_t<DPP, LaneMat<C>, Rows<LX, C>>;
 
 // out(o, sum_a mat[o][a] x[a]) for the LXD rows o; every sum ascends in a from zero
-template <int LX, int LXD, bool DPP, typename C, typename F>
-__device__ __forceinline__ void line_up(Mat<LX, C, DPP> mat, const C (&x)[LX], F out)
+template <int LX, int LXD, typename C, typename F>
+__device__ __forceinline__ void line_up(Rows<LX, C> mat, const C (&x)[LX], F out) { rows_up<LXD>(mat, x, out); }
+template <int LX, int LXD, typename C, typename F>
+__device__ __forceinline__ void line_up(LaneMat<C> mat, const C (&x)[LX], F out)
 {
-    constexpr int RB = Mat<LX, C, DPP>::RB;
 #pragma unroll
-    for (int o = 0; o < LXD; o += RB) {
-        C s[RB];
+    for (int o = 0; o < LXD; o += 3) {
+        C s[3], c[3];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) s[k] = 0;
-        if constexpr (DPP) {
-            C c[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) c[k] = mat.p[(o + k < LXD ? o + k : o) * LX];
-            up_row<LX, C>(s, c, x);
-            if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2])::"memory");
-        } else {
-            C c[RB][LX];
-            mat.load(o, LXD, c);
-#pragma unroll
-            for (int a = 0; a < LX; ++a)
-#pragma unroll
-                for (int k = 0; k < RB; ++k) s[k] += c[k][a] * x[a];
-#pragma unroll
-            for (int k = 0; k < RB; ++k) keep(s[k]);
+        for (int k = 0; k < 3; ++k) {
+            s[k] = 0;
+            c[k] = mat.p[(o + k < LXD ? o + k : o) * LX];
         }
+        up_row<LX, C>(s, c, x);
+        // (fp64: the next rows' entries stay unread till here, or V and T spill)
+        if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2])::"memory");
 #pragma unroll
-        for (int k = 0; k < RB; ++k)
+        for (int k = 0; k < 3; ++k)
             if (o + k < LXD) out(o + k, s[k]);
     }
 }
 // y[a] = sum_o mat[o][a] in(o), ascending in o from zero
-template <int LX, int LXD, bool DPP, typename C, typename F>
-__device__ __forceinline__ void line_down(Mat<LX, C, DPP> mat, F in, C (&y)[LX])
+template <int LX, int LXD, typename C, typename F>
+__device__ __forceinline__ void line_down(Rows<LX, C> mat, F in, C (&y)[LX]) { rows_down<LXD>(mat, in, y); }
+template <int LX, int LXD, typename C, typename F>
+__device__ __forceinline__ void line_down(LaneMat<C> mat, F in, C (&y)[LX])
 {
-    constexpr int RB = Mat<LX, C, DPP>::RB;
 #pragma unroll
     for (int a = 0; a < LX; ++a) y[a] = 0;
 #pragma unroll
-    for (int o = 0; o < LXD; o += RB) {
-        if constexpr (DPP) {
-            C c[3], v[3];
+    for (int o = 0; o < LXD; o += 3) {
+        C c[3], v[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                c[k] = mat.p[(o + k < LXD ? o + k : o) * LX];
-                v[k] = o + k < LXD ? in(o + k) : (C)0;
-                if (o + k >= LXD) c[k] = (C)0;   // past the last row nothing is added
-            }
-            down_row<LX, C>(y, c, v);
-            if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(y[0])::"memory");
-        } else {
-            C c[RB][LX];
-            mat.load(o, LXD, c);
-#pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                if (o + k >= LXD) continue;
-                const C v = in(o + k);
-#pragma unroll
-                for (int a = 0; a < LX; ++a) y[a] += c[k][a] * v;
-            }
-#pragma unroll
-            for (int a = 0; a < LX; ++a) keep(y[a]);
+        for (int k = 0; k < 3; ++k) {
+            c[k] = o + k < LXD ? mat.p[(o + k) * LX] : (C)0;   // past the last row nothing is added
+            v[k] = o + k < LXD ? in(o + k) : (C)0;
         }
+        down_row<LX, C>(y, c, v);
+        if constexpr (sizeof(C) == 8) asm volatile("" : "+v"(y[0])::"memory");
     }
 }
 
@@ -495,7 +444,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
 #pragma unroll
             for (int a = 0; a < LX; ++a) x[a] = (C)xu[a];
             C* y = sY + (tl / LX) * LXD * LJ + tl % LX;
-            line_up<LX, LXD, DPP>(mat, x, [&](int o, C v) { y[o * LJ] = v; });
+            line_up<LX, LXD>(mat, x, [&](int o, C v) { y[o * LJ] = v; });
         }
     };
     // second index: dst[k][j'][i'] = sum_b mat[j'][b] sY[k][i'][b], line q = (k, i')
@@ -507,7 +456,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
 #pragma unroll
             for (int b = 0; b < LX; ++b) x[b] = y[b];
             C* o2 = dst + (q / LXD) * NN + q % LXD;
-            line_up<LX, LXD, DPP>(mat, x, [&](int o, C v) { o2[o * LXD] = v; });
+            line_up<LX, LXD>(mat, x, [&](int o, C v) { o2[o * LXD] = v; });
         }
     };
     const bool fine = t < NN;
@@ -565,7 +514,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
     for (int c = 0; c < 3; ++c) {
         C x[LX];
         third_in(sIP + c * LX * NN, x);
-        line_up<LX, LXD, DPP>(mI, x, [&](int k, C v) {
+        line_up<LX, LXD>(mI, x, [&](int k, C v) {
             const int g = c * LR + k;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -598,7 +547,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
             }
             C x[LX];
             third_in(src, x);
-            line_up<LX, LXD, DPP>(kind == 2 ? mD : mI, x, [&](int k, C v) { T[k] = fma(V[kind][k], v, T[k]); });
+            line_up<LX, LXD>(kind == 2 ? mD : mI, x, [&](int k, C v) { T[k] = fma(V[kind][k], v, T[k]); });
             // (the next write to sB or sIP comes after another barrier: every
             // kind that uses sB passes the one behind its first index)
         };
@@ -607,7 +556,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
         add(std::integral_constant<int, K2>());
         if (!D::TIGHT && f < 2) load_u(f + 1);
         C z[LX];
-        line_down<LX, LXD, DPP>(mI, [&](int k) { return T[k]; }, z);
+        line_down<LX, LXD>(mI, [&](int k) { return T[k]; }, z);
         block_sync_lds();   // sB has been read
         if (fine) {
 #pragma unroll
@@ -619,7 +568,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
             const int q = lane_of(q0, LX * LXD);
             const C* src = sB + (q / LXD) * NN + q % LXD;
             C y[LX];
-            line_down<LX, LXD, DPP>(mI, [&](int o) { return src[o * LXD]; }, y);
+            line_down<LX, LXD>(mI, [&](int o) { return src[o * LXD]; }, y);
             C* dst = sY + (q / LXD) * LX * LP + q % LXD;
 #pragma unroll
             for (int b = 0; b < LX; ++b) dst[b * LP] = y[b];
@@ -629,7 +578,7 @@ __global__ void __launch_bounds__((Dn<LX, C>::NT), (Dn<LX, C>::WPE)) conv_dealia
         if (t0 < NL) {
             const C* src = sY + tl * LP;
             C y[LX];
-            line_down<LX, LXD, DPP>(mI, [&](int o) { return src[o]; }, y);
+            line_down<LX, LXD>(mI, [&](int o) { return src[o]; }, y);
             SEM_GLOBAL double* o = op_out(R, io, F_BN, f) + (long long)e * N3 + t * LX;
             if (t < NL) {
 #pragma unroll

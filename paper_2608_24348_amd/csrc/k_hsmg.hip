@@ -15,19 +15,20 @@
 // A_c^+: exact solve of the order-1 operator off the constant mode, by fast
 // diagonalisation on the nx ny nz corner nodes.
 //
-// One apply = 8 launches, every one gated per request:
+// One apply = 5 launches (7 for a large coarse grid), every one gated per request:
 //   hs_down   (fine FDM solve -> F_HSF; fine->middle restriction -> F_HRM)
 //   hs_mid    (sum copies of F_HRM; middle FDM -> F_HSM; middle->coarse -> F_HC8)
-//   hs_cgath  (coarse rhs on unique corner nodes -> F_HCA)
-//   hs_cxy, hs_cz, hs_cxy (coarse S^T along x and y, then z with the
-//             eigenvalue scaling and S along z, then S along y and x)
+//   hs_csmall (coarse rhs on unique corner nodes, S^T, eigenvalue scaling, S
+//             -> F_HCB), or for large grids
+//   hs_cxy, hs_cz, hs_cxy (coarse rhs, S^T along x and y -> F_HCB; z with the
+//             scaling and S along z -> F_HCA; S along x and y -> F_HCB)
 //   hs_midup  (z_m = summed F_HSM / count + trilinear coarse correction -> F_HZM)
 //   hs_up     (z = summed F_HSF / count + J3 z_m -> F_HZ and Z_J of F_HZS)
 // It runs in the Arnoldi steps only: the cycle end forms x += sum_j y_j Z_j
 // from the kept Z_j (M is linear, so this is x += M^{-1} V y).
 // The copy sums use index arithmetic on the periodic box in an order shared
 // by all copies of a node, so every copy receives the identical value.
-#include "k_common.h"
+#include "k_lines.h"
 
 namespace semk {
 
@@ -45,37 +46,52 @@ __device__ __forceinline__ Cand cand(int i, int ex, int n, int N)
     return c;
 }
 
-// sum of the copies of node (i,j,k) of element (ex,ey,ez) in the [E][L^3]
-// field f (AVG: divided by their number)
-template <int L, bool AVG = false>
-__device__ __forceinline__ double box_sum(const SEM_GLOBAL double* f, const int* nel, int ex, int ey, int ez,
-                                          int i, int j, int k)
+// v[k] = sum of the copies of node (i,j,k) of element (ex,ey,ez) in the
+// [E][L^3] field f, lower element first along z, then y, then x; returns
+// 1 / (copies in a layer of elements), exact.  The one to four (y, x) neighbour
+// columns are read one after the other, the points of one together (a loop over
+// the copies of a point waits for each).  At k = 0 and N they add the lower
+// layer's copies first, the upper's follow.
+template <int L>
+__device__ __forceinline__ double copies(const SEM_GLOBAL double* f, const int* nel, int ex, int ey, int ez,
+                                         int i, int j, double (&v)[L])
 {
-    constexpr int N = L - 1, L3 = L * L * L;
-    const Cand cx = cand(i, ex, nel[0], N), cy = cand(j, ey, nel[1], N), cz = cand(k, ez, nel[2], N);
-    double s = 0.0;
-    // fixed trip counts keep the candidate arrays in registers
+    constexpr int N = L - 1, L2 = L * L, L3 = L2 * L;
+    const int nx = nel[0], ny = nel[1], nz = nel[2], nxy = nx * ny;
+    const Cand cx = cand(i, ex, nx, N), cy = cand(j, ey, ny, N);
+    const int zd = nxy * (ez == 0 ? nz - 1 : ez - 1), zu = nxy * (ez + 1 == nz ? 0 : ez + 1);
+    double w0[4], wN[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        if (c >= cz.n) break;
+    for (int k = 0; k < L; ++k) v[k] = 0.0;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (b >= cy.n) break;
+    for (int h = 0; h < 4; ++h) {
+        const int b = h >> 1, a = h & 1;
+        w0[h] = wN[h] = 0.0;      // a +0 changes no bit of a sum that began with one
+        if (b < cy.n && a < cx.n) {
+            const int exy = cx.e[a] + nx * cy.e[b], in = cx.i[a] + L * cy.i[b];
+            const SEM_GLOBAL double* c = f + (long long)(exy + nxy * ez) * L3 + in;
+            const double d0 = f[(long long)(exy + zd) * L3 + in + L2 * N];
+            wN[h] = f[(long long)(exy + zu) * L3 + in];
+            double x[L];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                if (a >= cx.n) break;
-                const long long e = cx.e[a] + (long long)nel[0] * (cy.e[b] + (long long)nel[1] * cz.e[c]);
-                s += f[e * L3 + cx.i[a] + L * (cy.i[b] + L * cz.i[c])];
-            }
+            for (int k = 0; k < L; ++k) x[k] = c[L2 * k];
+            w0[h] = x[0];
+            x[0] = d0;
+#pragma unroll
+            for (int k = 0; k < L; ++k) v[k] += x[k];
         }
     }
-    return AVG ? s / (double)(cx.n * cy.n * cz.n) : s;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        v[0] += w0[h];
+        v[N] += wN[h];
+    }
+    return (cx.n == 2 ? 0.5 : 1.0) * (cy.n == 2 ? 0.5 : 1.0);
 }
 
 __device__ __forceinline__ double inv_mult(int i, int j, int k, int N)
 {
-    const int m = (i == 0 || i == N ? 2 : 1) * (j == 0 || j == N ? 2 : 1) * (k == 0 || k == N ? 2 : 1);
-    return 1.0 / (double)m;
+    return (i == 0 || i == N ? 0.5 : 1.0) * (j == 0 || j == N ? 0.5 : 1.0) * (k == 0 || k == N ? 0.5 : 1.0);
 }
 
 // Fast-diagonalisation solve of one element at order L - 1.  Thread (i, j)
@@ -164,74 +180,109 @@ __device__ __forceinline__ void elem_xyz(int e, const int* nel, int& ex, int& ey
 
 // ---------------------------------------------------------------- fine level, down
 // r = s_J V_J (basis storage TB)
+//
+// Bound by memory (V in, the local solution out, a quarter for r_m).  Every stage
+// is a contraction of whole lines in place: sA[k][j][i] in rows of an odd pitch,
+// sC[k][j][a] the restriction's part, which the x, y and z stages take along with
+// the solve's.  Two LDS reads per multiply-add had cost, us a launch: fp64 20^3,
+// LX = 10 138 -> 46 (28 for the bytes), 32^3, LX = 8 137 -> under 65; 12 requests
+// of 4..9^3, LX = 6 14.1 -> 10.5.
 template <int LX, typename TB>
 __global__ void __launch_bounds__(LX * LX) hs_down_kernel(Batch bt, int gate)
 {
-    constexpr int LM = hs_lxm(LX), L2 = LX * LX, L3 = L2 * LX, N = LX - 1;
-    __shared__ double sA[L3], sB[L3];
-    __shared__ double sS[3 * L2], sLam[3 * LX], sJ[LX * LM];
+    constexpr int LM = hs_lxm(LX), L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1, PM = LM | 1;
+    __shared__ double sA[L2 * P], sC[L2 * PM];
     const int g = blockIdx.x;
     const int ri = find_req(bt.el, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     const int e = g - bt.el[ri];
     if (!gate_ok(R, gate)) return;
-    const int t = threadIdx.x, i = t % LX, j = t / LX;
+    const int t = threadIdx.x, q = t % LX, p = t / LX;
     const HsOff o = hs_off(LX, R->nel);
-    const SEM_GLOBAL double* tb = gfield<double>(R, F_HST);
-    for (int q = t; q < 3 * L2; q += L2) sS[q] = tb[o.Sf + q];
-    for (int q = t; q < 3 * LX; q += L2) sLam[q] = tb[o.Lf + q];
-    for (int q = t; q < LX * LM; q += L2) sJ[q] = tb[o.J + q];
+    const double* tb = (const double*)gfield<double>(R, F_HST);
+    Rows<LX, double> Sx, Sy, Sz;
+    Rows<LM, double> Jm;
+    Sx.set(tb + o.Sf);
+    Sy.set(tb + o.Sf + L2);
+    Sz.set(tb + o.Sf + 2 * L2);
+    Jm.set(tb + o.J);
+    const double lij = gp(tb)[o.Lf + q] + gp(tb)[o.Lf + LX + p];   // of column (i, j) = (q, p)
 
     const long long base = (long long)e * L3;
-    double v[LX];
     {
         const int J = gp(R->I)[I_GJ];
         const double sc = gp(R->S)[S_GVS + J];
         const SEM_GLOBAL TB* V = gfield<TB>(R, F_V) + (long long)J * R->np;
+        double v[LX];
 #pragma unroll
-        for (int k = 0; k < LX; ++k) v[k] = sc * (double)V[base + i + LX * (j + LX * k)];
+        for (int k = 0; k < LX; ++k) v[k] = sc * (double)V[base + t + L2 * k];
+#pragma unroll
+        for (int k = 0; k < LX; ++k) sA[(k * LX + p) * P + q] = v[k];
     }
-
-    // restriction to the middle level: t = J^T J^T J^T (r / mult)
-    __syncthreads();
+    block_sync_lds();
+    {   // x: line (j, k) = (q, p)
+        double* x = sA + t * P;
+        double v[LX], y[LX], m[LM];
 #pragma unroll
-    for (int k = 0; k < LX; ++k) sA[k * L2 + j * LX + i] = v[k] * inv_mult(i, j, k, N);
-    __syncthreads();
-    if (i < LM) {
-        // x: sB[k][j][a] = sum_q J[q][a] sA[k][j][q], a = i
+        for (int a = 0; a < LX; ++a) v[a] = x[a];
+        rows_down<LX>(Sx, [&](int a) { return v[a]; }, y);
 #pragma unroll
-        for (int k = 0; k < LX; ++k) {
-            double s = 0.0;
+        for (int a = 0; a < LX; ++a) x[a] = y[a];
+        rows_down<LX>(Jm, [&](int a) { return v[a] * inv_mult(a, q, p, N); }, m);
 #pragma unroll
-            for (int q = 0; q < LX; ++q) s += sJ[q * LM + i] * sA[k * L2 + j * LX + q];
-            sB[k * L2 + j * LX + i] = s;
+        for (int a = 0; a < LM; ++a) sC[t * PM + a] = m[a];
+    }
+    block_sync_lds();
+    {   // y: line (i, k) = (q, p); of the restriction (a, k), a = t % LM
+        double* x = sA + p * LX * P + q;
+        double y[LX], m[LM];
+        rows_down<LX>(Sy, [&](int b) { return x[b * P]; }, y);
+#pragma unroll
+        for (int b = 0; b < LX; ++b) x[b * P] = y[b];
+        if (t < LM * LX) {
+            double* c = sC + (t / LM) * LX * PM + t % LM;
+            rows_down<LX>(Jm, [&](int b) { return c[b * PM]; }, m);
+#pragma unroll
+            for (int b = 0; b < LM; ++b) c[b * PM] = m[b];
         }
     }
-    __syncthreads();
-    if (i < LM && j < LM) {
-        // y then z for output column (a, b) = (i, j)
-        double col[LX];
+    block_sync_lds();
+    {   // z, the scaling and z back: column (i, j); of the restriction (a, b)
+        double* x = sA + p * P + q;
+        double y[LX];
+        rows_down<LX>(Sz, [&](int c) { return x[c * LX * P]; }, y);
 #pragma unroll
-        for (int k = 0; k < LX; ++k) {
-            double s = 0.0;
+        for (int k = 0; k < LX; ++k) y[k] = y[k] / (lij + gp(tb)[o.Lf + 2 * LX + k]);
+        rows_up<LX>(Sz, y, [&](int k, double v) { x[k * LX * P] = v; });
+        if (t < LM * LM) {
+            const double* c = sC + (t / LM) * PM + t % LM;
+            double m[LM];
+            rows_down<LX>(Jm, [&](int k) { return c[k * LX * PM]; }, m);
+            SEM_GLOBAL double* out = gfieldw<double>(R, F_HRM) + (long long)e * LM * LM * LM + t;
 #pragma unroll
-            for (int q = 0; q < LX; ++q) s += sJ[q * LM + j] * sB[k * L2 + q * LX + i];
-            col[k] = s;
-        }
-        SEM_GLOBAL double* out = gfieldw<double>(R, F_HRM) + (long long)e * LM * LM * LM;
-#pragma unroll
-        for (int c = 0; c < LM; ++c) {
-            double s = 0.0;
-#pragma unroll
-            for (int k = 0; k < LX; ++k) s += sJ[k * LM + c] * col[k];
-            out[i + LM * (j + LM * c)] = s;
+            for (int k = 0; k < LM; ++k) out[LM * LM * k] = m[k];
         }
     }
-    // fine local solve
-    fdm_solve<LX>(v, sS, sLam, sA, sB, i, j);
-    SEM_GLOBAL double* u = gfieldw<double>(R, F_HSF);
+    block_sync_lds();
+    {   // y back
+        double* x = sA + p * LX * P + q;
+        double v[LX];
 #pragma unroll
-    for (int k = 0; k < LX; ++k) u[base + i + LX * (j + LX * k)] = v[k];
+        for (int b = 0; b < LX; ++b) v[b] = x[b * P];
+        rows_up<LX>(Sy, v, [&](int b, double s) { x[b * P] = s; });
+    }
+    block_sync_lds();
+    {   // x back
+        double* x = sA + t * P;
+        double v[LX];
+#pragma unroll
+        for (int a = 0; a < LX; ++a) v[a] = x[a];
+        rows_up<LX>(Sx, v, [&](int a, double s) { x[a] = s; });
+    }
+    block_sync_lds();
+    SEM_GLOBAL double* u = gfieldw<double>(R, F_HSF) + base + t;
+#pragma unroll
+    for (int k = 0; k < LX; ++k) u[L2 * k] = sA[(k * LX + p) * P + q];
 }
 
 // ---------------------------------------------------------------- middle level, down
@@ -261,8 +312,7 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_mid_kernel(Batch bt,
     const SEM_GLOBAL double* rm = gfield<double>(R, F_HRM);
     double v[LM];
     // the assembled middle residual: sum of the element contributions
-#pragma unroll
-    for (int k = 0; k < LM; ++k) v[k] = box_sum<LM>(rm, R->nel, ex, ey, ez, i, j, k);
+    copies<LM>(rm, R->nel, ex, ey, ez, i, j, v);
     // coarse restriction of this element: c8 = Jc^T Jc^T Jc^T (r_m / mult)
     {
         double c0 = 0.0, c1 = 0.0;
@@ -293,101 +343,164 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_mid_kernel(Batch bt,
 }
 
 // ---------------------------------------------------------------- coarse level
-// unique corner node q = cx + nx (cy + ny cz) gathers the corner
-// contributions of its 8 elements
-__global__ void __launch_bounds__(256) hs_cgath_kernel(Batch bt, int gate)
+// unique corner node (cx, cy, cz): the sum of the contributions of its 8 elements
+__device__ __forceinline__ double corner_sum(const SEM_GLOBAL double* c8, int nx, int ny, int nz, int cx, int cy, int cz)
 {
-    const int ri = blockIdx.y;
-    const ReqDesc* R = bt.r[ri];
-    if (!gate_ok(R, gate)) return;
-    const int nx = R->nel[0], ny = R->nel[1], nz = R->nel[2];
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nx * ny * nz) return;
-    const int cx = q % nx, cy = (q / nx) % ny, cz = q / (nx * ny);
-    const SEM_GLOBAL double* c8 = gfield<double>(R, F_HC8);
-    double s = 0.0;
-    for (int c = 0; c < 2; ++c)
-        for (int b = 0; b < 2; ++b)
-            for (int a = 0; a < 2; ++a) {
-                const int ex = (cx - a + nx) % nx, ey = (cy - b + ny) % ny, ez = (cz - c + nz) % nz;
-                s += c8[(long long)(ex + nx * (ey + ny * ez)) * 8 + a + 2 * (b + 2 * c)];
-            }
-    gfieldw<double>(R, F_HCA)[q] = s;
+    const int xl = cx == 0 ? nx - 1 : cx - 1, yl = cy == 0 ? ny - 1 : cy - 1, zl = cz == 0 ? nz - 1 : cz - 1;
+    double v[8], s = 0.0;
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+        const int e = (h & 1 ? xl : cx) + nx * ((h & 2 ? yl : cy) + ny * (h & 4 ? zl : cz));
+        v[h] = c8[(long long)e * 8 + h];
+    }
+#pragma unroll
+    for (int h = 0; h < 8; ++h) s += v[h];
+    return s;
 }
 
-// coarse fast diagonalisation, x and y directions of one z-plane per
-// workgroup (grid.x = z index): fwd: out = (S_y^T x S_x^T) in, else
-// out = (S_y x S_x) in
-__global__ void __launch_bounds__(256) hs_cxy_kernel(Batch bt, int lx, int fwd, int src, int dst, int gate)
+// Coarse fast diagonalisation, x and y directions of HS_CW columns x of one
+// z-plane per workgroup (grid.x = z, grid.z = columns): FWD: out = (S_y^T x
+// S_x^T) of the gathered corner sums, else out = (S_y x S_x) in.  A plane alone
+// (32 workgroups at 32^3) leaves the chip idle behind two serial sums with their
+// matrices in memory: 8.5 us a launch at 20^3, now 7.0 with the gather (was a
+// launch of 4.8) and 4.8 back.
+#define HS_CW 8
+template <bool FWD>
+__global__ void __launch_bounds__(256) hs_cxy_kernel(Batch bt, int lx, int src, int dst, int gate)
 {
-    __shared__ double sP[HS_CPLANE], sQ[HS_CPLANE];
+    __shared__ double sP[HS_CPLANE], sY[HS_CPLANE], sX[HS_NELMAX * HS_CW], sQ[HS_NELMAX * HS_CW];
     const ReqDesc* R = bt.r[blockIdx.y];
     if (!gate_ok(R, gate)) return;
     const int nx = R->nel[0], ny = R->nel[1], nz = R->nel[2];
-    const int cz = blockIdx.x;
-    if (cz >= nz) return;
+    const int cz = blockIdx.x, x0 = blockIdx.z * HS_CW;
+    if (cz >= nz || x0 >= nx) return;
+    const int nw = nx - x0 < HS_CW ? nx - x0 : HS_CW, np = nx * ny;
     const HsOff o = hs_off(lx, R->nel);
     const SEM_GLOBAL double* tb = gfield<double>(R, F_HST);
     const SEM_GLOBAL double* Sx = tb + o.Sc[0];
     const SEM_GLOBAL double* Sy = tb + o.Sc[1];
-    const SEM_GLOBAL double* in = gfield<double>(R, src) + (long long)cz * nx * ny;
-    const int np = nx * ny;
-    for (int q = threadIdx.x; q < np; q += blockDim.x) sP[q] = in[q];
+    const SEM_GLOBAL double* in = gfield<double>(R, src);
+    for (int q = threadIdx.x; q < np; q += blockDim.x)
+        sP[q] = FWD ? corner_sum(in, nx, ny, nz, q % nx, q / nx, cz) : in[(long long)cz * np + q];
+    // sX[a][x], sY[b][y]: the entry that multiplies input a (b) of output x (y)
+    for (int q = threadIdx.x; q < nx * nw; q += blockDim.x) {
+        const int x = q % nw, a = q / nw;
+        sX[q] = FWD ? Sx[a * nx + x0 + x] : Sx[(x0 + x) * nx + a];
+    }
+    for (int q = threadIdx.x; q < ny * ny; q += blockDim.x) {
+        const int y = q % ny, b = q / ny;
+        sY[q] = FWD ? Sy[q] : Sy[y * ny + b];
+    }
     __syncthreads();
-    for (int q = threadIdx.x; q < np; q += blockDim.x) {
-        const int x = q % nx, y = q / nx;
+    for (int q = threadIdx.x; q < nw * ny; q += blockDim.x) {
+        const int x = q % nw, y = q / nw;
         double s = 0.0;
-        for (int a = 0; a < nx; ++a) s += (fwd ? Sx[a * nx + x] : Sx[x * nx + a]) * sP[y * nx + a];
+#pragma unroll 4
+        for (int a = 0; a < nx; ++a) s += sX[a * nw + x] * sP[y * nx + a];
         sQ[q] = s;
     }
     __syncthreads();
-    SEM_GLOBAL double* out = gfieldw<double>(R, dst) + (long long)cz * nx * ny;
-    for (int q = threadIdx.x; q < np; q += blockDim.x) {
-        const int x = q % nx, y = q / nx;
+    SEM_GLOBAL double* out = gfieldw<double>(R, dst) + (long long)cz * np + x0;
+    for (int q = threadIdx.x; q < nw * ny; q += blockDim.x) {
+        const int x = q % nw, y = q / nw;
         double s = 0.0;
-        for (int b = 0; b < ny; ++b) s += (fwd ? Sy[b * ny + y] : Sy[y * ny + b]) * sQ[b * nx + x];
-        out[q] = s;
+#pragma unroll 4
+        for (int b = 0; b < ny; ++b) s += sY[b * ny + y] * sQ[b * nw + x];
+        out[y * nx + x] = s;
     }
 }
 
-// coarse fast diagonalisation, z direction of one y-row per workgroup
-// (grid.x = y index): S_z^T, division by the eigenvalue sums (the constant
-// mode is dropped), S_z
+// coarse fast diagonalisation, z direction of HS_CW columns x of one y-row per
+// workgroup (grid.x = y, grid.z = columns): S_z^T, division by the eigenvalue
+// sums (the constant mode is dropped), S_z
 __global__ void __launch_bounds__(256) hs_cz_kernel(Batch bt, int lx, int src, int dst, int gate)
 {
-    __shared__ double sP[HS_CPLANE], sQ[HS_CPLANE];
+    __shared__ double sZ[HS_NELMAX * (HS_NELMAX + 1)], sP[HS_NELMAX * HS_CW], sQ[HS_NELMAX * HS_CW];
     const ReqDesc* R = bt.r[blockIdx.y];
     if (!gate_ok(R, gate)) return;
     const int nx = R->nel[0], ny = R->nel[1], nz = R->nel[2];
-    const int cy = blockIdx.x;
-    if (cy >= ny) return;
+    const int cy = blockIdx.x, x0 = blockIdx.z * HS_CW;
+    if (cy >= ny || x0 >= nx) return;
+    const int nw = nx - x0 < HS_CW ? nx - x0 : HS_CW, pz = nz | 1;
     const HsOff o = hs_off(lx, R->nel);
     const SEM_GLOBAL double* tb = gfield<double>(R, F_HST);
     const SEM_GLOBAL double* Sz = tb + o.Sc[2];
-    const SEM_GLOBAL double* in = gfield<double>(R, src);
-    const int np = nx * nz;                 // (x, z) of row cy, x fastest
-    for (int q = threadIdx.x; q < np; q += blockDim.x) {
-        const int x = q % nx, z = q / nx;
-        sP[q] = in[x + (long long)nx * (cy + (long long)ny * z)];
-    }
+    const SEM_GLOBAL double* in = gfield<double>(R, src) + x0 + (long long)nx * cy;
+    for (int q = threadIdx.x; q < nw * nz; q += blockDim.x) sP[q] = in[q % nw + (long long)nx * ny * (q / nw)];
+    for (int q = threadIdx.x; q < nz * nz; q += blockDim.x) sZ[q / nz * pz + q % nz] = Sz[q];
     __syncthreads();
     const double ly = tb[o.Lc[1] + cy];
-    for (int q = threadIdx.x; q < np; q += blockDim.x) {
-        const int x = q % nx, z = q / nx;
+    for (int q = threadIdx.x; q < nw * nz; q += blockDim.x) {
+        const int x = q % nw, z = q / nw;
         double s = 0.0;
-        for (int c = 0; c < nz; ++c) s += Sz[c * nz + z] * sP[c * nx + x];
-        if (x == R->hs_c0[0] && cy == R->hs_c0[1] && z == R->hs_c0[2]) s = 0.0;
-        else s /= tb[o.Lc[0] + x] + ly + tb[o.Lc[2] + z];
+#pragma unroll 4
+        for (int c = 0; c < nz; ++c) s += sZ[c * pz + z] * sP[c * nw + x];
+        if (x0 + x == R->hs_c0[0] && cy == R->hs_c0[1] && z == R->hs_c0[2]) s = 0.0;
+        else s /= tb[o.Lc[0] + x0 + x] + ly + tb[o.Lc[2] + z];
         sQ[q] = s;
     }
     __syncthreads();
-    SEM_GLOBAL double* out = gfieldw<double>(R, dst);
-    for (int q = threadIdx.x; q < np; q += blockDim.x) {
-        const int x = q % nx, z = q / nx;
+    SEM_GLOBAL double* out = gfieldw<double>(R, dst) + x0 + (long long)nx * cy;
+    for (int q = threadIdx.x; q < nw * nz; q += blockDim.x) {
+        const int x = q % nw, z = q / nw;
         double s = 0.0;
-        for (int c = 0; c < nz; ++c) s += Sz[z * nz + c] * sQ[c * nx + x];
-        out[x + (long long)nx * (cy + (long long)ny * z)] = s;
+#pragma unroll 4
+        for (int c = 0; c < nz; ++c) s += sZ[z * pz + c] * sQ[c * nw + x];
+        out[x + (long long)nx * ny * z] = s;
     }
+}
+
+// The whole coarse solve of a small grid in one workgroup: the same sums, one
+// launch for the gather's and three more.
+#define HS_CSN 16       // points per direction
+#define HS_CSM 1024     // points
+__global__ void __launch_bounds__(1024) hs_csmall_kernel(Batch bt, int lx, int gate)
+{
+    constexpr int P = HS_CSN + 1;
+    __shared__ double sA[HS_CSM], sB[HS_CSM], sS[3][HS_CSN * P], sL[3][HS_CSN];
+    const ReqDesc* R = bt.r[blockIdx.x];
+    if (!gate_ok(R, gate)) return;
+    const int nx = R->nel[0], ny = R->nel[1], nz = R->nel[2], np = nx * ny, n = np * nz;
+    const HsOff o = hs_off(lx, R->nel);
+    const SEM_GLOBAL double* tb = gfield<double>(R, F_HST);
+    const SEM_GLOBAL double* c8 = gfield<double>(R, F_HC8);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int m = R->nel[d];
+        for (int q = threadIdx.x; q < m * m; q += blockDim.x) sS[d][q / m * P + q % m] = tb[o.Sc[d] + q];
+        for (int q = threadIdx.x; q < m; q += blockDim.x) sL[d][q] = tb[o.Lc[d] + q];
+    }
+    for (int q = threadIdx.x; q < n; q += blockDim.x) sA[q] = corner_sum(c8, nx, ny, nz, q % nx, q / nx % ny, q / np);
+    __syncthreads();
+    // to[q] = sum_a S[a][x] from[..a..] (fwd) or S[x][a] (back) along direction d
+    auto along = [&](int d, bool fwd, const double* from, auto put) {
+        const int m = R->nel[d], st = d == 0 ? 1 : d == 1 ? nx : np;
+        for (int q = threadIdx.x; q < n; q += blockDim.x) {
+            const int x = q / st % m;
+            const double* f = from + q - x * st;
+            const double* S = sS[d] + (fwd ? x : x * P);
+            const int ss = fwd ? P : 1;
+            double s = 0.0;
+#pragma unroll 4
+            for (int a = 0; a < m; ++a) s += S[a * ss] * f[a * st];
+            put(q, s);
+        }
+        __syncthreads();
+    };
+    auto toA = [&](int q, double s) { sA[q] = s; };
+    auto toB = [&](int q, double s) { sB[q] = s; };
+    along(0, true, sA, toB);
+    along(1, true, sB, toA);
+    along(2, true, sA, [&](int q, double s) {
+        const int x = q % nx, y = q / nx % ny, z = q / np;
+        if (x == R->hs_c0[0] && y == R->hs_c0[1] && z == R->hs_c0[2]) s = 0.0;
+        else s /= sL[0][x] + sL[1][y] + sL[2][z];
+        sB[q] = s;
+    });
+    along(2, false, sB, toA);
+    along(0, false, sA, toB);
+    SEM_GLOBAL double* out = gfieldw<double>(R, F_HCB);
+    along(1, false, sB, [&](int q, double s) { out[q] = s; });
 }
 
 // ---------------------------------------------------------------- middle level, up
@@ -419,7 +532,8 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_midup_kernel(Batch b
     __syncthreads();
     if (!live) return;
     const double* E8 = sE + el * 8;
-    const SEM_GLOBAL double* sm = gfield<double>(R, F_HSM);
+    double v[LM];
+    const double rm = copies<LM>(gfield<double>(R, F_HSM), R->nel, ex, ey, ez, i, j, v);
     SEM_GLOBAL double* zm = gfieldw<double>(R, F_HZM) + (long long)e * L3;
 #pragma unroll
     for (int k = 0; k < LM; ++k) {
@@ -428,18 +542,21 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_midup_kernel(Batch b
             for (int b = 0; b < 2; ++b)
                 for (int a = 0; a < 2; ++a)
                     p += E8[a + 2 * (b + 2 * c)] * sJc[i * 2 + a] * sJc[j * 2 + b] * sJc[k * 2 + c];
-        zm[i + LM * (j + LM * k)] = box_sum<LM, true>(sm, R->nel, ex, ey, ez, i, j, k) + p;
+        zm[i + LM * (j + LM * k)] = v[k] * (k == 0 || k == LM - 1 ? 0.5 * rm : rm) + p;   // the product is exact
     }
 }
 
 // ---------------------------------------------------------------- fine level, up
 // z -> F_HZ (the operator's input) and Z_J of F_HZS (the cycle end's x update), type TZ
+//
+// Bound by memory and the latency of the copies; us a launch, lines and batched
+// copies against one copy at a time: fp64 20^3, LX = 10 95 -> 68 (40 for the
+// bytes), 32^3, LX = 8 169 -> 126, fp32 basis 92 -> 67; 12 of 4..9^3 17.4 -> 10.5.
 template <int LX, typename TZ>
 __global__ void __launch_bounds__(LX * LX) hs_up_kernel(Batch bt, int gate)
 {
-    constexpr int LM = hs_lxm(LX), L2 = LX * LX, L3 = L2 * LX;
-    __shared__ double sA[LM * LM * LM], sB[LM * LM * LX];
-    __shared__ double sJ[LX * LM];
+    constexpr int LM = hs_lxm(LX), LM2 = LM * LM, L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1;
+    __shared__ double sA[LM2 * P], sB[LM * L2];   // [c][b][i], [c][j][i]
     const int g = blockIdx.x;
     const int ri = find_req(bt.el, bt.n, g);
     const ReqDesc* R = bt.r[ri];
@@ -447,45 +564,39 @@ __global__ void __launch_bounds__(LX * LX) hs_up_kernel(Batch bt, int gate)
     if (!gate_ok(R, gate)) return;
     const int t = threadIdx.x, i = t % LX, j = t / LX;
     const HsOff o = hs_off(LX, R->nel);
-    const SEM_GLOBAL double* tb = gfield<double>(R, F_HST);
-    for (int q = t; q < LX * LM; q += L2) sJ[q] = tb[o.J + q];
-    const SEM_GLOBAL double* zm = gfield<double>(R, F_HZM) + (long long)e * LM * LM * LM;
-    for (int q = t; q < LM * LM * LM; q += L2) sA[q] = zm[q];
-    __syncthreads();
-    // x: sB[c][b][i] = sum_a J[i][a] zm[c][b][a]
-    if (j < LM) {
-#pragma unroll
-        for (int c = 0; c < LM; ++c) {
-            double s = 0.0;
-#pragma unroll
-            for (int a = 0; a < LM; ++a) s += sJ[i * LM + a] * sA[c * LM * LM + j * LM + a];
-            sB[c * LM * LX + j * LX + i] = s;
-        }
-    }
-    __syncthreads();
-    double col[LM];
-#pragma unroll
-    for (int c = 0; c < LM; ++c) {
-        double s = 0.0;
-#pragma unroll
-        for (int b = 0; b < LM; ++b) s += sJ[j * LM + b] * sB[c * LM * LX + b * LX + i];
-        col[c] = s;
-    }
+    Rows<LM, double> Jm;
+    Jm.set((const double*)gfield<double>(R, F_HST) + o.J);
     int ex, ey, ez;
     elem_xyz(e, R->nel, ex, ey, ez);
-    const SEM_GLOBAL double* sf = gfield<double>(R, F_HSF);
-    const long long base = (long long)e * L3 + i + LX * j;
+    double v[LX];
+    const double rm = copies<LX>(gfield<double>(R, F_HSF), R->nel, ex, ey, ez, i, j, v);
+    // J3 z_m by lines: x (c, b), y (c, i), z (i, j)
+    const SEM_GLOBAL double* zm = gfield<double>(R, F_HZM) + (long long)e * LM2 * LM;
+    double x[LM];
+    if (t < LM2) {
+#pragma unroll
+        for (int a = 0; a < LM; ++a) x[a] = zm[t * LM + a];
+        rows_up<LX>(Jm, x, [&](int q, double p) { sA[t * P + q] = p; });
+    }
+    block_sync_lds();
+    if (t < LM * LX) {
+        const double* c = sA + (t / LX) * LM * P + t % LX;
+#pragma unroll
+        for (int b = 0; b < LM; ++b) x[b] = c[b * P];
+        rows_up<LX>(Jm, x, [&](int q, double p) { sB[(t / LX) * L2 + q * LX + t % LX] = p; });
+    }
+    block_sync_lds();
+#pragma unroll
+    for (int c = 0; c < LM; ++c) x[c] = sB[c * L2 + t];
+    const long long base = (long long)e * L3 + t;
     SEM_GLOBAL TZ* hz = gfieldw<TZ>(R, F_HZ) + base;
     SEM_GLOBAL TZ* zj = gfieldw<TZ>(R, F_HZS) + (long long)gp(R->I)[I_GJ] * R->np + base;
-#pragma unroll
-    for (int k = 0; k < LX; ++k) {
-        double p = 0.0;
-#pragma unroll
-        for (int c = 0; c < LM; ++c) p += sJ[k * LM + c] * col[c];
-        const TZ z = (TZ)(box_sum<LX, true>(sf, R->nel, ex, ey, ez, i, j, k) + p);
+    rows_up<LX>(Jm, x, [&](int k, double p) {
+        // (a product with a power of two is exact: fused or not, the same bits)
+        const TZ z = (TZ)(v[k] * (k == 0 || k == N ? 0.5 * rm : rm) + p);
         hz[L2 * k] = z;
         zj[L2 * k] = z;
-    }
+    });
 }
 
 template <int LX>
@@ -499,13 +610,19 @@ static void hsmg_go(const Batch& b, int tb, int gate, hipStream_t s)
     constexpr int EP = hs_mepb(LM);
     const int nmb = b.hm[b.n];
     hipLaunchKernelGGL((hs_mid_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
-    const dim3 cg((b.ncmax + 255) / 256, b.n);
-    hipLaunchKernelGGL(hs_cgath_kernel, cg, dim3(256), 0, s, b, gate);
-    // coarse fast diagonalisation: F_HCA -> (x, y fwd) F_HCB -> (z) F_HCA -> (x, y inv) F_HCB
-    const dim3 cp(b.cnmax, b.n);
-    hipLaunchKernelGGL(hs_cxy_kernel, cp, dim3(256), 0, s, b, LX, 1, (int)F_HCA, (int)F_HCB, gate);
-    hipLaunchKernelGGL(hs_cz_kernel, cp, dim3(256), 0, s, b, LX, (int)F_HCB, (int)F_HCA, gate);
-    hipLaunchKernelGGL(hs_cxy_kernel, cp, dim3(256), 0, s, b, LX, 0, (int)F_HCA, (int)F_HCB, gate);
+    // One workgroup while a thread has one point of the grid and the three
+    // matrices fit beside it: 12 grids of 4..9^3 10.0 us against 17.5 in four
+    // launches, 5 of 4..8^3 5.9 against 14.4.  At 20^3 (8000 points) the three
+    // launches take 17.6 us and one workgroup would have eight rounds.
+    if (b.cmax <= HS_CSN && b.ncmax <= HS_CSM) {
+        hipLaunchKernelGGL(hs_csmall_kernel, dim3(b.n), dim3(1024), 0, s, b, LX, gate);
+    } else {
+        // F_HC8 -> (gather, x, y fwd) F_HCB -> (z) F_HCA -> (x, y back) F_HCB
+        const dim3 cp(b.cmax, b.n, (b.cmax + HS_CW - 1) / HS_CW);
+        hipLaunchKernelGGL((hs_cxy_kernel<true>), cp, dim3(256), 0, s, b, LX, (int)F_HC8, (int)F_HCB, gate);
+        hipLaunchKernelGGL(hs_cz_kernel, cp, dim3(256), 0, s, b, LX, (int)F_HCB, (int)F_HCA, gate);
+        hipLaunchKernelGGL((hs_cxy_kernel<false>), cp, dim3(256), 0, s, b, LX, (int)F_HCA, (int)F_HCB, gate);
+    }
     hipLaunchKernelGGL((hs_midup_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
     if (tb == P64) hipLaunchKernelGGL((hs_up_kernel<LX, double>), dim3(ne), dim3(LX * LX), 0, s, b, gate);
     else hipLaunchKernelGGL((hs_up_kernel<LX, float>), dim3(ne), dim3(LX * LX), 0, s, b, gate);

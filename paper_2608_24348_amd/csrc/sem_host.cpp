@@ -598,7 +598,7 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
     b.gq[0] = 0;
     b.gate = -1;
     b.ncmax = 0;
-    b.cnmax = 0;
+    b.cmax = 0;
     for (int i = 0; i < n; ++i) {
         sem_ctx* c = ctxs[i];
         b.eb[i + 1] = b.eb[i] + c->nb;
@@ -611,7 +611,7 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
         b.gl[i + 1] = b.gl[i] + c->mesh.nel[1] * c->mesh.nel[2] * (c->lx - 1);
         b.gq[i + 1] = b.gq[i] + c->mesh.nel[1] * c->mesh.nel[2] * ((c->lx - 1 + 3) / 4);
         b.ncmax = std::max(b.ncmax, c->mesh.nel[0] * c->mesh.nel[1] * c->mesh.nel[2]);
-        b.cnmax = std::max(b.cnmax, std::max(c->mesh.nel[1], c->mesh.nel[2]));
+        b.cmax = std::max(b.cmax, std::max(c->mesh.nel[0], std::max(c->mesh.nel[1], c->mesh.nel[2])));
         b.r[i] = c->ddesc;
     }
     return b;

@@ -214,7 +214,7 @@ struct Batch {
     int gate;                   // element operators (conv, opgrad, wdiv, diagnostics): I index that must
                                 // be nonzero for a request's blocks to run, or -1
     int ncmax;                  // largest coarse HSMG grid (nx ny nz) of the batch
-    int cnmax;                  // largest ny or nz of the batch (coarse-pass workgroups)
+    int cmax;                   // largest element count along a direction of the batch
     const ReqDesc* r[SEM_MAXB];
 };
 

@@ -1,0 +1,42 @@
+"""The coarse solve of the multigrid preconditioner has two forms: one workgroup
+for a small grid, three launches for a batch that holds a larger one.  Both take
+the same sums, so a request's solution does not depend on what it is batched
+with, bit for bit (no tolerance); the larger one is held to the oracle."""
+import pytest
+
+from oracle import OracleMesh
+from paper_2608_24348_amd import sem
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# odd and even extents, one column group of 8 and several, both sides of 16 elements and of 1024 nodes
+SMALL = [(2, 2, 2), (16, 4, 16), (9, 10, 11), (3, 16, 2)]
+LARGE = [(17, 2, 3), (2, 25, 4), (2, 3, 33), (16, 16, 5)]
+
+
+def _ctx(nel, tier):
+    return sem.Context(sem.mesh_desc(nel, 4), sem.flow_desc(mode=sem.MODE_POISSON, pres_tol=1e-8, hsmg=1), sem.tier(tier), device="cuda:0")
+
+
+def _rhs(c, seed):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    return c.mass(torch.randn(c.np, dtype=torch.float64, device="cuda:0", generator=g))
+
+
+@pytest.mark.parametrize("tier", ["fp64", "fp32b"])
+@pytest.mark.parametrize("q", range(4))
+def test_coarse_solve_forms_agree(q, tier):
+    small, large = _ctx(SMALL[q], tier), _ctx(LARGE[q], tier)
+    rhs = [_rhs(small, 1), _rhs(large, 2)]
+    alone = [torch.empty_like(r) for r in rhs]
+    both = [torch.empty_like(r) for r in rhs]
+    it = [sem.poisson_solve([c], [r], [x])[0]["iters"] for c, r, x in zip((small, large), rhs, alone)]
+    st = sem.poisson_solve([small, large], rhs, both)
+    assert [s["iters"] for s in st] == it
+    for a, b in zip(alone, both):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b)
+    small.close()
+    large.close()
