@@ -341,11 +341,13 @@ template <int LX, typename C, int A = 0> __device__ __forceinline__ void down_ro
 
 // a 1D matrix as line_up and line_down take it: by DPP this lane's entry of row 0 in LDS
 template <typename C> struct LaneMat { const C* p; };
-template <int LX, typename C, bool DPP> using Mat = std::conditional_t<DPP, LaneMat<C>, Rows<LX, C>>;
+// (or RB rows at a time: more, up to the scalar registers, lose 2% at LX = 7, 8)
+template <typename C> constexpr int dl_rb = sizeof(C) == 8 ? 3 : 6;
+template <int LX, typename C, bool DPP> using Mat = std::conditional_t<DPP, LaneMat<C>, Rows<LX, C, dl_rb<C>>>;
 
 // out(o, sum_a mat[o][a] x[a]) for the LXD rows o; every sum ascends in a from zero
 template <int LX, int LXD, typename C, typename F>
-__device__ __forceinline__ void line_up(Rows<LX, C> mat, const C (&x)[LX], F out) { rows_up<LXD>(mat, x, out); }
+__device__ __forceinline__ void line_up(Rows<LX, C, dl_rb<C>> mat, const C (&x)[LX], F out) { rows_up<LXD>(mat, x, out); }
 template <int LX, int LXD, typename C, typename F>
 __device__ __forceinline__ void line_up(LaneMat<C> mat, const C (&x)[LX], F out)
 {
@@ -367,7 +369,7 @@ __device__ __forceinline__ void line_up(LaneMat<C> mat, const C (&x)[LX], F out)
 }
 // y[a] = sum_o mat[o][a] in(o), ascending in o from zero
 template <int LX, int LXD, typename C, typename F>
-__device__ __forceinline__ void line_down(Rows<LX, C> mat, F in, C (&y)[LX]) { rows_down<LXD>(mat, in, y); }
+__device__ __forceinline__ void line_down(Rows<LX, C, dl_rb<C>> mat, F in, C (&y)[LX]) { rows_down<LXD>(mat, in, y); }
 template <int LX, int LXD, typename C, typename F>
 __device__ __forceinline__ void line_down(LaneMat<C> mat, F in, C (&y)[LX])
 {

@@ -186,18 +186,23 @@ __device__ __forceinline__ void elem_xyz(int e, const int* nel, int& ex, int& ey
 // sC[k][j][a] the restriction's part, which the x, y and z stages take along with
 // the solve's.  Two LDS reads per multiply-add had cost, us a launch: fp64 20^3,
 // LX = 10 138 -> 46 (28 for the bytes), 32^3, LX = 8 137 -> under 65; 12 requests
-// of 4..9^3, LX = 6 14.1 -> 10.5.
+// of 4..9^3, LX = 6 14.1 -> 9.4.
 template <int LX, typename TB>
-__global__ void __launch_bounds__(LX * LX) hs_down_kernel(Batch bt, int gate)
+__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_down_kernel(Batch bt, int gate)
 {
     constexpr int LM = hs_lxm(LX), L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1, PM = LM | 1;
-    __shared__ double sA[L2 * P], sC[L2 * PM];
+    constexpr int EP = hs_fepb(LX);
+    __shared__ double sAs[EP * L2 * P], sCs[EP * L2 * PM];
     const int g = blockIdx.x;
-    const int ri = find_req(bt.el, bt.n, g);
+    const int ri = find_req(bt.hf, bt.n, g);
     const ReqDesc* R = bt.r[ri];
-    const int e = g - bt.el[ri];
     if (!gate_ok(R, gate)) return;
-    const int t = threadIdx.x, q = t % LX, p = t / LX;
+    const int el = EP > 1 ? threadIdx.x / L2 : 0, t = threadIdx.x - el * L2, q = t % LX, p = t / LX;
+    const int e0 = (g - bt.hf[ri]) * EP + el;
+    const bool live = e0 < R->E;
+    const int e = live ? e0 : 0;   // lanes past the last element work on element 0 and store nothing
+    double* const sA = sAs + el * L2 * P;
+    double* const sC = sCs + el * L2 * PM;
     const HsOff o = hs_off(LX, R->nel);
     const double* tb = (const double*)gfield<double>(R, F_HST);
     Rows<LX, double> Sx, Sy, Sz;
@@ -260,7 +265,8 @@ __global__ void __launch_bounds__(LX * LX) hs_down_kernel(Batch bt, int gate)
             rows_down<LX>(Jm, [&](int k) { return c[k * LX * PM]; }, m);
             SEM_GLOBAL double* out = gfieldw<double>(R, F_HRM) + (long long)e * LM * LM * LM + t;
 #pragma unroll
-            for (int k = 0; k < LM; ++k) out[LM * LM * k] = m[k];
+            for (int k = 0; k < LM; ++k)
+                if (live) out[LM * LM * k] = m[k];
         }
     }
     block_sync_lds();
@@ -282,7 +288,8 @@ __global__ void __launch_bounds__(LX * LX) hs_down_kernel(Batch bt, int gate)
     block_sync_lds();
     SEM_GLOBAL double* u = gfieldw<double>(R, F_HSF) + base + t;
 #pragma unroll
-    for (int k = 0; k < LX; ++k) u[L2 * k] = sA[(k * LX + p) * P + q];
+    for (int k = 0; k < LX; ++k)
+        if (live) u[L2 * k] = sA[(k * LX + p) * P + q];
 }
 
 // ---------------------------------------------------------------- middle level, down
@@ -551,18 +558,23 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_midup_kernel(Batch b
 //
 // Bound by memory and the latency of the copies; us a launch, lines and batched
 // copies against one copy at a time: fp64 20^3, LX = 10 95 -> 68 (40 for the
-// bytes), 32^3, LX = 8 169 -> 126, fp32 basis 92 -> 67; 12 of 4..9^3 17.4 -> 10.5.
+// bytes), 32^3, LX = 8 169 -> 126, fp32 basis 92 -> 67; 12 of 4..9^3 17.4 -> 8.8.
 template <int LX, typename TZ>
-__global__ void __launch_bounds__(LX * LX) hs_up_kernel(Batch bt, int gate)
+__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_up_kernel(Batch bt, int gate)
 {
     constexpr int LM = hs_lxm(LX), LM2 = LM * LM, L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1;
-    __shared__ double sA[LM2 * P], sB[LM * L2];   // [c][b][i], [c][j][i]
+    constexpr int EP = hs_fepb(LX);
+    __shared__ double sAs[EP * LM2 * P], sBs[EP * LM * L2];   // [c][b][i], [c][j][i]
     const int g = blockIdx.x;
-    const int ri = find_req(bt.el, bt.n, g);
+    const int ri = find_req(bt.hf, bt.n, g);
     const ReqDesc* R = bt.r[ri];
-    const int e = g - bt.el[ri];
     if (!gate_ok(R, gate)) return;
-    const int t = threadIdx.x, i = t % LX, j = t / LX;
+    const int el = EP > 1 ? threadIdx.x / L2 : 0, t = threadIdx.x - el * L2, i = t % LX, j = t / LX;
+    const int e0 = (g - bt.hf[ri]) * EP + el;
+    const bool live = e0 < R->E;
+    const int e = live ? e0 : 0;
+    double* const sA = sAs + el * LM2 * P;
+    double* const sB = sBs + el * LM * L2;
     const HsOff o = hs_off(LX, R->nel);
     Rows<LM, double> Jm;
     Jm.set((const double*)gfield<double>(R, F_HST) + o.J);
@@ -594,8 +606,10 @@ __global__ void __launch_bounds__(LX * LX) hs_up_kernel(Batch bt, int gate)
     rows_up<LX>(Jm, x, [&](int k, double p) {
         // (a product with a power of two is exact: fused or not, the same bits)
         const TZ z = (TZ)(v[k] * (k == 0 || k == N ? 0.5 * rm : rm) + p);
-        hz[L2 * k] = z;
-        zj[L2 * k] = z;
+        if (live) {
+            hz[L2 * k] = z;
+            zj[L2 * k] = z;
+        }
     });
 }
 
@@ -603,10 +617,10 @@ template <int LX>
 static void hsmg_go(const Batch& b, int tb, int gate, hipStream_t s)
 {
     constexpr int LM = hs_lxm(LX);
-    const int ne = b.el[b.n];
+    const int ne = b.hf[b.n], nt = hs_fepb(LX) * LX * LX;
     if (ne == 0) return;
-    if (tb == P64) hipLaunchKernelGGL((hs_down_kernel<LX, double>), dim3(ne), dim3(LX * LX), 0, s, b, gate);
-    else hipLaunchKernelGGL((hs_down_kernel<LX, float>), dim3(ne), dim3(LX * LX), 0, s, b, gate);
+    if (tb == P64) hipLaunchKernelGGL((hs_down_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, gate);
+    else hipLaunchKernelGGL((hs_down_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, gate);
     constexpr int EP = hs_mepb(LM);
     const int nmb = b.hm[b.n];
     hipLaunchKernelGGL((hs_mid_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
@@ -624,8 +638,8 @@ static void hsmg_go(const Batch& b, int tb, int gate, hipStream_t s)
         hipLaunchKernelGGL((hs_cxy_kernel<false>), cp, dim3(256), 0, s, b, LX, (int)F_HCA, (int)F_HCB, gate);
     }
     hipLaunchKernelGGL((hs_midup_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
-    if (tb == P64) hipLaunchKernelGGL((hs_up_kernel<LX, double>), dim3(ne), dim3(LX * LX), 0, s, b, gate);
-    else hipLaunchKernelGGL((hs_up_kernel<LX, float>), dim3(ne), dim3(LX * LX), 0, s, b, gate);
+    if (tb == P64) hipLaunchKernelGGL((hs_up_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, gate);
+    else hipLaunchKernelGGL((hs_up_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, gate);
 }
 
 void launch_hsmg(const Batch& b, int lx, int tb, int gate, hipStream_t s)

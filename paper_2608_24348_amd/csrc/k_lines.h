@@ -13,9 +13,9 @@ namespace semk {
 template <typename C> __device__ __forceinline__ void keep(C& v) { asm volatile("" : "+v"(v)); }
 
 // row-major matrix of NC columns in device memory
-template <int NC, typename C> struct Rows {
+template <int NC, typename C, int NB = 72 / (NC * (int)sizeof(C) / 4)> struct Rows {   // a batch: up to 72 scalar registers
+    static constexpr int RB = NB;
     unsigned lo, hi;
-    static constexpr int RB = sizeof(C) == 8 ? 3 : 6;
     __device__ __forceinline__ void set(const void* p)
     {
         lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
@@ -37,10 +37,9 @@ template <int NC, typename C> struct Rows {
 };
 
 // out(o, sum_a mat[o][a] x[a]), o = 0 .. NR - 1
-template <int NR, int NC, typename C, typename F>
-__device__ __forceinline__ void rows_up(Rows<NC, C> mat, const C (&x)[NC], F out)
+template <int NR, int NC, typename C, int RB, typename F>
+__device__ __forceinline__ void rows_up(Rows<NC, C, RB> mat, const C (&x)[NC], F out)
 {
-    constexpr int RB = Rows<NC, C>::RB;
 #pragma unroll
     for (int o = 0; o < NR; o += RB) {
         C c[RB][NC], s[RB];
@@ -59,10 +58,9 @@ __device__ __forceinline__ void rows_up(Rows<NC, C> mat, const C (&x)[NC], F out
     }
 }
 // y[a] = sum_o mat[o][a] in(o)
-template <int NR, int NC, typename C, typename F>
-__device__ __forceinline__ void rows_down(Rows<NC, C> mat, F in, C (&y)[NC])
+template <int NR, int NC, typename C, int RB, typename F>
+__device__ __forceinline__ void rows_down(Rows<NC, C, RB> mat, F in, C (&y)[NC])
 {
-    constexpr int RB = Rows<NC, C>::RB;
 #pragma unroll
     for (int a = 0; a < NC; ++a) y[a] = 0;
 #pragma unroll

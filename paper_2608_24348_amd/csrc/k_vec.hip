@@ -331,15 +331,23 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) vec_kernel(Batch bt, VecArgs 
 // over unique nodes and the second subtracts that mean: a no-op in exact
 // arithmetic that keeps rounding (notably of fp32 operators) from feeding the
 // null direction into the basis.
+// a value that every lane holds, in scalar registers (the coefficients of a pass took 62 vector registers)
+__device__ __forceinline__ double scalar(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
 template <int NJ, int MODE, typename TB>
-__device__ __forceinline__ void gm_body(const ReqDesc* R, const PtRange& pr, double (&acc)[SEM_MAXM + 1], double& accm)
+__device__ __forceinline__ void gm_body(const ReqDesc* R, const PtRange& pr, double* acc, double& accm)
 {
     const SEM_GLOBAL TB* V = fld<TB>(R, F_V);
     const long long np = R->np;
     double h[NJ];
 #pragma unroll
     for (int i = 0; i < NJ; ++i)
-        h[i] = (MODE == 1 ? gp(R->S)[S_GHC + i] : MODE == 2 ? gp(R->S)[S_GH2 + i] : 0.0) * gp(R->S)[S_GVS + i];
+        h[i] = scalar((MODE == 1 ? gp(R->S)[S_GHC + i] : MODE == 2 ? gp(R->S)[S_GH2 + i] : 0.0) * gp(R->S)[S_GVS + i]);
     const double mean = MODE == 1 ? gp(R->S)[S_GMEAN] : 0.0;
     auto w = fld<double>(R, F_GW);
     auto wd = fldw<double>(R, F_GWD);
@@ -403,10 +411,11 @@ __device__ __forceinline__ void gm_body(const ReqDesc* R, const PtRange& pr, dou
     F(1) F(2) F(3) F(4) F(5) F(6) F(7) F(8) F(9) F(10) F(11) F(12) F(13) F(14) F(15) F(16) F(17) F(18) \
     F(19) F(20) F(21) F(22) F(23) F(24) F(25) F(26) F(27) F(28) F(29) F(30) F(31)
 
-template <int MODE, typename TB>
+// CAP: the largest basis size J + 1 that the launch can meet (the rule is in launch_vec)
+template <int MODE, typename TB, int CAP>
 __global__ void __launch_bounds__(SEM_VEC_THREADS) gm_pass_kernel(Batch bt, int gate)
 {
-    constexpr int NV = SEM_MAXM + 1, NW = SEM_VEC_THREADS / 64, RS = 32;
+    constexpr int NV = MODE == 2 ? 1 : CAP, NW = SEM_VEC_THREADS / 64, RS = 32;
     __shared__ double red[NW * RS];
     __shared__ double redm[NW];
     const int g = blockIdx.x;
@@ -421,7 +430,7 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) gm_pass_kernel(Batch bt, int 
     for (int i = 0; i < NV; ++i) acc[i] = 0.0;
     double accm = 0.0;
     switch (J + 1) {
-#define GM_CASE(n) case n: gm_body<n, MODE, TB>(R, pr, acc, accm); break;
+#define GM_CASE(n) case n: if constexpr (n <= CAP) gm_body<n, MODE, TB>(R, pr, acc, accm); break;
         SEM_NJ_CASES(GM_CASE)
 #undef GM_CASE
     default: break;
@@ -432,9 +441,10 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) gm_pass_kernel(Batch bt, int 
         const double s = wave_sum(acc[0]);
         if (lane == 0) red[wid * RS] = s;
     } else {
-        double v[RS];
+        constexpr int NP = (NV + 3) / 4 * 4;
+        double v[NP];
 #pragma unroll
-        for (int i = 0; i < RS; ++i) v[i] = i < NV ? acc[i] : 0.0;
+        for (int i = 0; i < NP; ++i) v[i] = i < NV ? acc[i] : 0.0;
         wave_sums(v, nv, red + wid * RS);
     }
     if constexpr (MODE == 0) {
@@ -599,18 +609,22 @@ void launch_vec(const Batch& b, const VecArgs& a, hipStream_t s)
     dim3 blk(SEM_VEC_THREADS);
     if (grid.x == 0) return;
     switch (a.op) {
-    case V_GM_DOTS:
-        if (a.tb == P64) hipLaunchKernelGGL((gm_pass_kernel<0, double>), grid, blk, 0, s, b, a.gate);
-        else hipLaunchKernelGGL((gm_pass_kernel<0, float>), grid, blk, 0, s, b, a.gate);
-        return;
-    case V_GM_UPD_DOTS:
-        if (a.tb == P64) hipLaunchKernelGGL((gm_pass_kernel<1, double>), grid, blk, 0, s, b, a.gate);
-        else hipLaunchKernelGGL((gm_pass_kernel<1, float>), grid, blk, 0, s, b, a.gate);
-        return;
-    case V_GM_UPD_NORM:
-        if (a.tb == P64) hipLaunchKernelGGL((gm_pass_kernel<2, double>), grid, blk, 0, s, b, a.gate);
-        else hipLaunchKernelGGL((gm_pass_kernel<2, float>), grid, blk, 0, s, b, a.gate);
-        return;
+    // The smallest instance that holds the basis (a.f0: an upper bound of its
+    // size, < 0 none).  The instance for 31 vectors holds as many sums and loads
+    // a point: 152 registers, three waves a SIMD, and a batch of small requests
+    // waits in rounds; those for 8 and 16 run 4 to 8.  us a launch of the second
+    // pass, 12 requests of 4..9^3, N = 5, fp32 basis: 20.4 for all, now 10.3 (8),
+    // 17.3 (16), 13.7 (31, mostly idle); one of 20^3, bound by memory, the same.
+#define GM_GO(M, C)                                                                                              \
+    if (a.tb == P64) hipLaunchKernelGGL((gm_pass_kernel<M, double, C>), grid, blk, 0, s, b, a.gate);             \
+    else hipLaunchKernelGGL((gm_pass_kernel<M, float, C>), grid, blk, 0, s, b, a.gate);
+#define GM_CAPS(M)                                                                                               \
+    if (a.f0 > 0 && a.f0 <= 8) { GM_GO(M, 8) } else if (a.f0 > 0 && a.f0 <= 16) { GM_GO(M, 16) } else { GM_GO(M, SEM_MAXM + 1) }
+    case V_GM_DOTS: GM_CAPS(0) return;
+    case V_GM_UPD_DOTS: GM_CAPS(1) return;
+    case V_GM_UPD_NORM: GM_CAPS(2) return;
+#undef GM_CAPS
+#undef GM_GO
     case V_PR_ADOTS:
     case V_PR_GUESS:
     case V_PR_BDOTS:

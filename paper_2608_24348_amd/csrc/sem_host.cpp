@@ -594,6 +594,7 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
     b.vb[0] = 0;
     b.el[0] = 0;
     b.hm[0] = 0;
+    b.hf[0] = 0;
     b.gl[0] = 0;
     b.gq[0] = 0;
     b.gate = -1;
@@ -607,6 +608,8 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
         {
             const int mp = hs_mepb(hs_lxm(c->lx));
             b.hm[i + 1] = b.hm[i] + (c->E + mp - 1) / mp;
+            const int fp = hs_fepb(c->lx);
+            b.hf[i + 1] = b.hf[i] + (c->E + fp - 1) / fp;
         }
         b.gl[i + 1] = b.gl[i] + c->mesh.nel[1] * c->mesh.nel[2] * (c->lx - 1);
         b.gq[i + 1] = b.gq[i] + c->mesh.nel[1] * c->mesh.nel[2] * ((c->lx - 1 + 3) / 4);
@@ -854,8 +857,9 @@ void gmres_cycle_end(const Batch& b, int lx, const Resolved& r, bool hsmg, hipSt
 }
 
 // One Arnoldi step of GMRES(m); every kernel is gated so requests whose
-// cycle ended (or that converged) idle until the next cycle end.
-void gmres_arnoldi(const Batch& b, int lx, const Resolved& r, bool hsmg, hipStream_t s)
+// cycle ended (or that converged) idle until the next cycle end.  nj: an upper
+// bound of any request's basis size J + 1 in this step.
+void gmres_arnoldi(const Batch& b, int lx, const Resolved& r, bool hsmg, int nj, hipStream_t s)
 {
     if (hsmg) {
         // w = A M^{-1} V_J with z = M^{-1} V_J in HZ (basis storage precision)
@@ -886,15 +890,15 @@ void gmres_arnoldi(const Batch& b, int lx, const Resolved& r, bool hsmg, hipStre
     }
     {
         ProfScope ps(SEM_PROF_GM_DOTS, s);
-        vec(b, V_GM_DOTS, 1, P64, I_GARN, s, -1, -1, P64, r.tb, FIN_GM_H1);
+        vec(b, V_GM_DOTS, 1, P64, I_GARN, s, nj, -1, P64, r.tb, FIN_GM_H1);
     }
     {
         ProfScope ps(SEM_PROF_GM_UPD_DOTS, s);
-        vec(b, V_GM_UPD_DOTS, 1, P64, I_GARN, s, -1, -1, P64, r.tb, FIN_GM_H2);
+        vec(b, V_GM_UPD_DOTS, 1, P64, I_GARN, s, nj, -1, P64, r.tb, FIN_GM_H2);
     }
     {
         ProfScope ps(SEM_PROF_GM_UPD_NORM, s);
-        vec(b, V_GM_UPD_NORM, 1, P64, I_GARN, s, -1, -1, P64, r.tb, FIN_GM_COL);
+        vec(b, V_GM_UPD_NORM, 1, P64, I_GARN, s, nj, -1, P64, r.tb, FIN_GM_COL);
     }
 }
 
@@ -925,8 +929,10 @@ int gmres_advance(sem_ctx* const* ctxs, const Batch& b, hipStream_t s, int max_i
     while (done < max_iters) {
         const int k = std::min(K, max_iters - done);
         for (int q = 0; q < k; ++q) {
-            gmres_arnoldi(b, c0->lx, c0->rs, c0->flow.hsmg != 0, s);
             ++since;
+            // (a basis is no larger than the steps run so far; after a restart that
+            // some requests took alone, only m bounds it)
+            gmres_arnoldi(b, c0->lx, c0->rs, c0->flow.hsmg != 0, lockstep ? std::min(done + q + 1, m) : m, s);
             if (!lockstep || since == m || q == k - 1) {
                 gmres_cycle_end(b, c0->lx, c0->rs, c0->flow.hsmg != 0, s);
                 if (since == m) since = 0;
@@ -1512,7 +1518,7 @@ void fixed_step(sem_ctx* const* ctxs, const Batch& b, const Budget& g, double* h
     gmres_start(b, lx, r, hsmg, s);
     const int m = c0->flow.gmres_restart;
     for (int q = 0; q < g.kp; ++q) {
-        gmres_arnoldi(b, lx, r, hsmg, s);
+        gmres_arnoldi(b, lx, r, hsmg, std::min(q + 1, m), s);
         if ((q + 1) % m == 0 || q == g.kp - 1) gmres_cycle_end(b, lx, r, hsmg, s);
     }
     fin(b, FIN_COMMIT_CHECK, s);

@@ -209,6 +209,7 @@ struct Batch {
     int vb[SEM_MAXB + 1];       // prefix over point-wise blocks
     int el[SEM_MAXB + 1];       // prefix over elements (one-element-per-workgroup kernels)
     int hm[SEM_MAXB + 1];       // prefix over HSMG middle-level blocks (hs_mepb elements each)
+    int hf[SEM_MAXB + 1];       // prefix over HSMG fine-level blocks (hs_fepb elements each)
     int gl[SEM_MAXB + 1];       // prefix over row-form gather-scatter workgroups (one per x-line of elements and k)
     int gq[SEM_MAXB + 1];       // prefix over plane-form gather-scatter workgroups (one per x-line and 4 planes k)
     int gate;                   // element operators (conv, opgrad, wdiv, diagnostics): I index that must
@@ -231,6 +232,11 @@ __host__ __device__ constexpr int dl16_per_elem(int lx)
 // HSMG middle level: order N/2; its kernels take hs_mepb elements per workgroup
 __host__ __device__ constexpr int hs_lxm(int lx) { return (lx - 1) / 2 + 1; }
 __host__ __device__ constexpr int hs_mepb(int lm) { return 64 / (lm * lm) > 0 ? 64 / (lm * lm) : 1; }
+
+// HSMG fine level: elements per workgroup.  A wave holds the lx^2 lines of one
+// element from lx = 8 on; below, elements share the waves (12 requests of 4..9^3,
+// lx = 6: 9.4 and 8.8 us a launch of hs_down and hs_up, one element each 9.9 and 10.5).
+__host__ __device__ constexpr int hs_fepb(int lx) { return lx <= 7 ? 256 / (lx * lx) : 1; }
 
 // offsets (doubles) of the HSMG tables in F_HST: fine S (3 lx^2, S[c][i*lx+k] =
 // component i of eigenvector k), fine lambda (3 lx), middle S, middle lambda,
