@@ -386,7 +386,8 @@ struct sem_ctx {
     hipStream_t stream = nullptr;
     ReqDesc* ddesc = nullptr;
     ReqDesc hdesc;
-    int* hflags = nullptr;  // pinned host flags for polls
+    int* hflags = nullptr;  // pinned host flags for polls (SEM_MAXB), then the statistics of a batch
+    double* hstats() const { return (double*)(hflags + SEM_MAXB); }   // SEM_MAXB x SEM_NSTAT
     int device = 0;         // HIP device current at sem_bind
     MeshParams mp;
     // iteration counts of the previous step: where the host first reads the
@@ -1210,7 +1211,8 @@ int sem_bind(sem_ctx* c, void* dev_buf, size_t bytes, void* hip_stream)
     I[I_GMAXIT] = c->flow.pres_maxit;
     I[I_GM] = c->flow.gmres_restart;
     I[I_ALWAYS] = 1;
-    HIPCHK(hipHostMalloc((void**)&c->hflags, sizeof(int) * SEM_MAXB, hipHostMallocDefault));
+    static_assert(SEM_MAXB * sizeof(int) % sizeof(double) == 0, "the statistics follow the flags");
+    HIPCHK(hipHostMalloc((void**)&c->hflags, sizeof(int) * SEM_MAXB + sizeof(double) * SEM_MAXB * SEM_NSTAT, hipHostMallocDefault));
     HIPCHK(hipMemcpyAsync(c->ddesc, &d, sizeof(d), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(d.S, S.data(), sizeof(double) * NSCALAR, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(d.I, I.data(), sizeof(int) * NINT, hipMemcpyHostToDevice, s));
@@ -1407,6 +1409,14 @@ void launch_stats(const Batch& b, double* hs, hipStream_t s)
     fa.op = FIN_STATS; fa.gate = -1; fa.ncomp = 1; fa.f0 = 0; fa.host_flags = nullptr; fa.host_stats = hs;
     fa.gate2 = -1;
     launch_fin(b, fa, s);
+}
+
+// statistics of a solve from what FIN_STATS wrote (h holds one request's SEM_NSTAT)
+void solve_stats(const double* h, const sem_ctx* c, sem_solve_stats* st)
+{
+    st->iters = (int)h[10];
+    st->res = h[11];
+    st->status = h[12] != 0.0 ? SEM_ENAN : (h[11] > c->flow.pres_tol ? SEM_ENOTCONV : SEM_OK);
 }
 
 // explicit terms of a step and the residual of its velocity solve (both paths)
@@ -1843,17 +1853,11 @@ int sem_poisson_solve(sem_ctx* const* ctxs, int n, const void* const* rhs, void*
     for (int i = 0; i < n; ++i)
         HIPCHK(hipMemcpyAsync(sol[i], ctxs[i]->hdesc.f[F_GX], 8 * (size_t)ctxs[i]->np, hipMemcpyDeviceToDevice, s));
     if (stats) {
-        for (int i = 0; i < n; ++i) {
-            int it = 0, nan = 0;
-            double res = 0;
-            HIPCHK(hipMemcpyAsync(&it, ctxs[i]->hdesc.I + I_GIT, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipMemcpyAsync(&nan, ctxs[i]->hdesc.I + I_NAN, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipMemcpyAsync(&res, ctxs[i]->hdesc.S + S_GBETA, sizeof(double), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
-            stats[i].iters = it;
-            stats[i].res = res;
-            stats[i].status = nan ? SEM_ENAN : (res > ctxs[i]->flow.pres_tol ? SEM_ENOTCONV : SEM_OK);
-        }
+        // one launch writes every request's statistics to pinned memory (three
+        // copies and a wait for each request took 0.6 of the 3.6 ms of a batch of 12)
+        launch_stats(b, c0->hstats(), s);
+        HIPCHK(hipStreamSynchronize(s));
+        for (int i = 0; i < n; ++i) solve_stats(c0->hstats() + (size_t)i * SEM_NSTAT, ctxs[i], stats + i);
     }
     return check_hip_last();
 }
@@ -1900,17 +1904,9 @@ int sem_poisson_finish(sem_ctx* c, void* sol, sem_solve_stats* st)
     hipStream_t s = c->stream;
     gmres_finish(b, s);
     if (sol) HIPCHK(hipMemcpyAsync(sol, c->hdesc.f[F_GX], 8 * (size_t)c->np, hipMemcpyDeviceToDevice, s));
-    int it = 0, nan = 0;
-    double res = 0;
-    HIPCHK(hipMemcpyAsync(&it, c->hdesc.I + I_GIT, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&nan, c->hdesc.I + I_NAN, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&res, c->hdesc.S + S_GBETA, sizeof(double), hipMemcpyDeviceToHost, s));
+    launch_stats(b, c->hstats(), s);
     HIPCHK(hipStreamSynchronize(s));
-    if (st) {
-        st->iters = it;
-        st->res = res;
-        st->status = nan ? SEM_ENAN : (res > c->flow.pres_tol ? SEM_ENOTCONV : SEM_OK);
-    }
+    if (st) solve_stats(c->hstats(), c, st);
     return check_hip_last();
 }
 
