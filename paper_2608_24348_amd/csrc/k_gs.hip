@@ -252,6 +252,10 @@ dssum_rows_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, 
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gl[bt.n]) return;
+    const int c = blockIdx.y;   // component
+    field = field >= 0 ? field + c : field;
+    gate = gate >= 0 ? gate + c : gate;
+    pslot = pslot >= 0 ? pslot + c : pslot;
     const int ri = find_req(bt.gl, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
@@ -448,6 +452,10 @@ dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gq[bt.n]) return;
+    const int c = blockIdx.y;   // component
+    field = field >= 0 ? field + c : field;
+    gate = gate >= 0 ? gate + c : gate;
+    pslot = pslot >= 0 ? pslot + c : pslot;
     const int ri = find_req(bt.gq, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
@@ -483,24 +491,22 @@ dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot
 // 0.237 against 0.242 ms; three workgroups: 0.658 ms).
 constexpr unsigned GS_PLANES_LDS = 32000;
 
-// one launch per component
+// One launch: the components in turn (blockIdx.y; grid.x is a multiple of the
+// eight XCDs, so each keeps its placement).  Three components of 5 requests of
+// 4..8^3, N = 7: 20 us in a launch each, 12 in one; of 32^3: 164 and 161.
 template <typename T, typename A, int V, bool MASS>
 static void dssum_go(const Batch& b, int field, int ncomp, int gate, void* raw, hipStream_t s, int pslot,
                      bool planes, const void* mf)
 {
     const int nblk = planes ? b.gq[b.n] : b.gl[b.n];
     const int per = (nblk + 7) / 8;
-    dim3 grid(8 * per);
-    for (int c = 0; c < ncomp; ++c) {
-        const int f = field >= 0 ? field + c : field, gt = gate < 0 ? gate : gate + c;
-        const int ps = pslot >= 0 ? pslot + c : -1;
-        if (planes)
-            hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b, f,
-                               gt, raw, per, ps, mf);
-        else
-            hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), 0, s, b, f, gt, raw, per,
-                               ps, mf);
-    }
+    const dim3 grid(8 * per, ncomp);
+    if (planes)
+        hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b, field,
+                           gate, raw, per, pslot, mf);
+    else
+        hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), 0, s, b, field, gate, raw, per,
+                           pslot, mf);
 }
 
 // Word size and form, as measured (a batch shares one lx):
