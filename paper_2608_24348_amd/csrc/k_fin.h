@@ -54,13 +54,12 @@ static __device__ void slot_sums(const ReqDesc* R, const int (&slot)[NS], double
         for (int k = 0; k < NS; ++k) red[(t >> 6) * NS + k] = s[k];
     }
     __syncthreads();
-    if (t == 0) {
 #pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            double v = 0.0;
+    for (int k = 0; k < NS; ++k) {
+        double v = 0.0;   // (defined in every thread: a caller returns it)
+        if (t == 0)
             for (int w = 0; w < bd / 64; ++w) v += red[w * NS + k];
-            out[k] = v;
-        }
+        out[k] = v;
     }
     __syncthreads();
 }
