@@ -245,17 +245,19 @@ template <bool MASS> __device__ __forceinline__ GsMass gs_mass(const ReqDesc* R,
 // Workgroup p runs task block (p % 8) * per + p / 8, so each XCD walks one
 // contiguous range; within a request the blocks go (ez, k, ey), so the two
 // blocks that share the lines of a row j = 0 are neighbours on one XCD.
-template <typename T, typename A, int V, bool MASS = false>
+template <typename T, typename A, int V, bool MASS = false, bool MC = false>
 __global__ void __launch_bounds__(SEM_GS_THREADS)
 dssum_rows_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, const void* mf = nullptr)
 {
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gl[bt.n]) return;
-    const int c = blockIdx.y;   // component
-    field = field >= 0 ? field + c : field;
-    gate = gate >= 0 ? gate + c : gate;
-    pslot = pslot >= 0 ? pslot + c : pslot;
+    if constexpr (MC) {   // component blockIdx.y
+        const int c = blockIdx.y;
+        field += c;
+        gate = gate >= 0 ? gate + c : gate;
+        pslot = pslot >= 0 ? pslot + c : pslot;
+    }
     const int ri = find_req(bt.gl, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
@@ -445,17 +447,19 @@ __device__ __forceinline__ void gs_plane_task(SEM_GLOBAL char* const* lp, unsign
 
 // Workgroup p runs task block (p % 8) * per + p / 8 (one x-line and four
 // planes k, a wave each); within a request the blocks go (ez, k / 4, ey).
-template <typename T, typename A, int V, bool MASS = false>
+template <typename T, typename A, int V, bool MASS = false, bool MC = false>
 __global__ void __launch_bounds__(SEM_GS_THREADS)
 dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, const void* mf = nullptr)
 {
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gq[bt.n]) return;
-    const int c = blockIdx.y;   // component
-    field = field >= 0 ? field + c : field;
-    gate = gate >= 0 ? gate + c : gate;
-    pslot = pslot >= 0 ? pslot + c : pslot;
+    if constexpr (MC) {   // component blockIdx.y
+        const int c = blockIdx.y;
+        field += c;
+        gate = gate >= 0 ? gate + c : gate;
+        pslot = pslot >= 0 ? pslot + c : pslot;
+    }
     const int ri = find_req(bt.gq, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
@@ -493,7 +497,8 @@ constexpr unsigned GS_PLANES_LDS = 32000;
 
 // One launch: the components in turn (blockIdx.y; grid.x is a multiple of the
 // eight XCDs, so each keeps its placement).  Three components of 5 requests of
-// 4..8^3, N = 7: 20 us in a launch each, 12 in one; of 32^3: 164 and 161.
+// 4..8^3, N = 7: 20 us in a launch each, 12 in one; of 32^3: 164 and 161.  A
+// single component keeps an instance of its own (0.2 of 5 us).
 template <typename T, typename A, int V, bool MASS>
 static void dssum_go(const Batch& b, int field, int ncomp, int gate, void* raw, hipStream_t s, int pslot,
                      bool planes, const void* mf)
@@ -501,12 +506,21 @@ static void dssum_go(const Batch& b, int field, int ncomp, int gate, void* raw, 
     const int nblk = planes ? b.gq[b.n] : b.gl[b.n];
     const int per = (nblk + 7) / 8;
     const dim3 grid(8 * per, ncomp);
-    if (planes)
-        hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b, field,
-                           gate, raw, per, pslot, mf);
-    else
-        hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MASS>), grid, dim3(SEM_GS_THREADS), 0, s, b, field, gate, raw, per,
-                           pslot, mf);
+#define DSSUM_GO(MC)                                                                                                   \
+    if (planes)                                                                                                        \
+        hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MASS, MC>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b,  \
+                           field, gate, raw, per, pslot, mf);                                                          \
+    else                                                                                                               \
+        hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MASS, MC>), grid, dim3(SEM_GS_THREADS), 0, s, b, field, gate,   \
+                           raw, per, pslot, mf);
+    if constexpr (!MASS) {
+        if (ncomp > 1) {
+            DSSUM_GO(true)
+            return;
+        }
+    }
+    DSSUM_GO(false)
+#undef DSSUM_GO
 }
 
 // Word size and form, as measured (a batch shares one lx):

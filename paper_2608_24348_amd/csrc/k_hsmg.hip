@@ -179,6 +179,11 @@ __device__ __forceinline__ void elem_xyz(int e, const int* nel, int& ex, int& ey
 }
 
 // ---------------------------------------------------------------- fine level, down
+// prefix over fine-level blocks (hs_fepb elements each), an argument of these
+// two kernels alone: every launch copies its arguments
+struct HsFine {
+    int p[SEM_MAXB + 1];
+};
 // r = s_J V_J (basis storage TB)
 //
 // Bound by memory (V in, the local solution out, a quarter for r_m).  Every stage
@@ -188,17 +193,17 @@ __device__ __forceinline__ void elem_xyz(int e, const int* nel, int& ex, int& ey
 // LX = 10 138 -> 46 (28 for the bytes), 32^3, LX = 8 137 -> under 65; 12 requests
 // of 4..9^3, LX = 6 14.1 -> 9.4.
 template <int LX, typename TB>
-__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_down_kernel(Batch bt, int gate)
+__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_down_kernel(Batch bt, HsFine hf, int gate)
 {
     constexpr int LM = hs_lxm(LX), L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1, PM = LM | 1;
     constexpr int EP = hs_fepb(LX);
     __shared__ double sAs[EP * L2 * P], sCs[EP * L2 * PM];
     const int g = blockIdx.x;
-    const int ri = find_req(bt.hf, bt.n, g);
+    const int ri = find_req(hf.p, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
     const int el = EP > 1 ? threadIdx.x / L2 : 0, t = threadIdx.x - el * L2, q = t % LX, p = t / LX;
-    const int e0 = (g - bt.hf[ri]) * EP + el;
+    const int e0 = (g - hf.p[ri]) * EP + el;
     const bool live = e0 < R->E;
     const int e = live ? e0 : 0;   // lanes past the last element work on element 0 and store nothing
     double* const sA = sAs + el * L2 * P;
@@ -560,17 +565,17 @@ __global__ void __launch_bounds__(hs_mepb(LM) * LM * LM) hs_midup_kernel(Batch b
 // copies against one copy at a time: fp64 20^3, LX = 10 95 -> 68 (40 for the
 // bytes), 32^3, LX = 8 169 -> 126, fp32 basis 92 -> 67; 12 of 4..9^3 17.4 -> 8.8.
 template <int LX, typename TZ>
-__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_up_kernel(Batch bt, int gate)
+__global__ void __launch_bounds__(hs_fepb(LX) * LX * LX) hs_up_kernel(Batch bt, HsFine hf, int gate)
 {
     constexpr int LM = hs_lxm(LX), LM2 = LM * LM, L2 = LX * LX, L3 = L2 * LX, N = LX - 1, P = LX | 1;
     constexpr int EP = hs_fepb(LX);
     __shared__ double sAs[EP * LM2 * P], sBs[EP * LM * L2];   // [c][b][i], [c][j][i]
     const int g = blockIdx.x;
-    const int ri = find_req(bt.hf, bt.n, g);
+    const int ri = find_req(hf.p, bt.n, g);
     const ReqDesc* R = bt.r[ri];
     if (!gate_ok(R, gate)) return;
     const int el = EP > 1 ? threadIdx.x / L2 : 0, t = threadIdx.x - el * L2, i = t % LX, j = t / LX;
-    const int e0 = (g - bt.hf[ri]) * EP + el;
+    const int e0 = (g - hf.p[ri]) * EP + el;
     const bool live = e0 < R->E;
     const int e = live ? e0 : 0;
     double* const sA = sAs + el * LM2 * P;
@@ -617,10 +622,14 @@ template <int LX>
 static void hsmg_go(const Batch& b, int tb, int gate, hipStream_t s)
 {
     constexpr int LM = hs_lxm(LX);
-    const int ne = b.hf[b.n], nt = hs_fepb(LX) * LX * LX;
+    HsFine hf;
+    hf.p[0] = 0;
+    for (int i = 0; i < b.n; ++i) hf.p[i + 1] = hf.p[i] + (b.el[i + 1] - b.el[i] + hs_fepb(LX) - 1) / hs_fepb(LX);
+    for (int i = b.n; i < SEM_MAXB; ++i) hf.p[i + 1] = hf.p[b.n];
+    const int ne = hf.p[b.n], nt = hs_fepb(LX) * LX * LX;
     if (ne == 0) return;
-    if (tb == P64) hipLaunchKernelGGL((hs_down_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, gate);
-    else hipLaunchKernelGGL((hs_down_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, gate);
+    if (tb == P64) hipLaunchKernelGGL((hs_down_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, hf, gate);
+    else hipLaunchKernelGGL((hs_down_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, hf, gate);
     constexpr int EP = hs_mepb(LM);
     const int nmb = b.hm[b.n];
     hipLaunchKernelGGL((hs_mid_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
@@ -638,8 +647,8 @@ static void hsmg_go(const Batch& b, int tb, int gate, hipStream_t s)
         hipLaunchKernelGGL((hs_cxy_kernel<false>), cp, dim3(256), 0, s, b, LX, (int)F_HCA, (int)F_HCB, gate);
     }
     hipLaunchKernelGGL((hs_midup_kernel<LM>), dim3(nmb), dim3(EP * LM * LM), 0, s, b, LX, gate);
-    if (tb == P64) hipLaunchKernelGGL((hs_up_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, gate);
-    else hipLaunchKernelGGL((hs_up_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, gate);
+    if (tb == P64) hipLaunchKernelGGL((hs_up_kernel<LX, double>), dim3(ne), dim3(nt), 0, s, b, hf, gate);
+    else hipLaunchKernelGGL((hs_up_kernel<LX, float>), dim3(ne), dim3(nt), 0, s, b, hf, gate);
 }
 
 void launch_hsmg(const Batch& b, int lx, int tb, int gate, hipStream_t s)

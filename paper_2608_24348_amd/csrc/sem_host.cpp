@@ -595,7 +595,6 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
     b.vb[0] = 0;
     b.el[0] = 0;
     b.hm[0] = 0;
-    b.hf[0] = 0;
     b.gl[0] = 0;
     b.gq[0] = 0;
     b.gate = -1;
@@ -609,8 +608,6 @@ semk::Batch make_batch(sem_ctx* const* ctxs, int n)
         {
             const int mp = hs_mepb(hs_lxm(c->lx));
             b.hm[i + 1] = b.hm[i] + (c->E + mp - 1) / mp;
-            const int fp = hs_fepb(c->lx);
-            b.hf[i + 1] = b.hf[i] + (c->E + fp - 1) / fp;
         }
         b.gl[i + 1] = b.gl[i] + c->mesh.nel[1] * c->mesh.nel[2] * (c->lx - 1);
         b.gq[i + 1] = b.gq[i] + c->mesh.nel[1] * c->mesh.nel[2] * ((c->lx - 1 + 3) / 4);

@@ -209,7 +209,6 @@ struct Batch {
     int vb[SEM_MAXB + 1];       // prefix over point-wise blocks
     int el[SEM_MAXB + 1];       // prefix over elements (one-element-per-workgroup kernels)
     int hm[SEM_MAXB + 1];       // prefix over HSMG middle-level blocks (hs_mepb elements each)
-    int hf[SEM_MAXB + 1];       // prefix over HSMG fine-level blocks (hs_fepb elements each)
     int gl[SEM_MAXB + 1];       // prefix over row-form gather-scatter workgroups (one per x-line of elements and k)
     int gq[SEM_MAXB + 1];       // prefix over plane-form gather-scatter workgroups (one per x-line and 4 planes k)
     int gate;                   // element operators (conv, opgrad, wdiv, diagnostics): I index that must
@@ -220,7 +219,7 @@ struct Batch {
 };
 
 // 16-bit fine-grid metric terms of the dealiased convection: lane-ordered for
-// the matrix-core kernel (lx <= 10), per element [tile][ac][g][m][r] with
+// a wave of fine lines (lx <= 10), per element [tile][ac][g][m][r] with
 // r fastest (one 8-byte load per lane and term), else natural [ac][point]
 __host__ __device__ constexpr int dl16_lane(int lx) { return lx <= 10 ? 1 : 0; }
 __host__ __device__ constexpr int dl16_per_elem(int lx)
