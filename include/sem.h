@@ -320,7 +320,7 @@ int sem_get_field(sem_ctx* ctx, int which, void* dst, int is_host);
 int sem_set_field(sem_ctx* ctx, int which, const void* src, int is_host);
 /* Mass matrix: out = B o f (element-local), plus dssum when flags &
  * SEM_ASSEMBLE (out then is the assembled load vector of f).  Device fp64
- * arrays of E*lx^3 values; asynchronous. */
+ * arrays of E*lx^3 values, which may be one array or overlap; asynchronous. */
 int sem_mass(sem_ctx* ctx, const double* f, double* out, int flags);
 
 /* Node fields for synthetic inputs: what = 0, 1, 2 writes the x, y or z

@@ -321,6 +321,46 @@ __global__ void __launch_bounds__(SEM_VEC_THREADS) vec_kernel(Batch bt, VecArgs 
     }
 }
 
+// ------------------------------------------------------------------ mass matrix on overlapping arrays
+// out = B o f where the two arrays share memory at different offsets, so that a
+// value written may be one still to be read.  One workgroup takes the points in
+// blocks, away from the array it writes over (ascending when out lies below f),
+// and reads a block whole before it writes it: the writes then meet only f
+// values of this block and of those before.  Such calls are rare; one CU moves
+// their 24 bytes per point.
+constexpr int MO_THREADS = 1024, MO_PTS = 8 * MO_THREADS;
+__global__ void __launch_bounds__(MO_THREADS) mass_overlap_kernel(Batch bt, const double* f_, double* out_)
+{
+    const ReqDesc* R = bt.r[0];
+    const SEM_GLOBAL double* f = gp(f_);
+    SEM_GLOBAL double* out = gp(out_);
+    auto B = fld<double>(R, F_B64);
+    const long long np = R->np, nblk = (np + MO_PTS - 1) / MO_PTS;
+    const bool up = (uintptr_t)out_ < (uintptr_t)f_;
+    for (long long q = 0; q < nblk; ++q) {
+        const long long p0 = (up ? q : nblk - 1 - q) * MO_PTS + threadIdx.x;
+        double v[MO_PTS / MO_THREADS];
+#pragma unroll
+        for (int u = 0; u < MO_PTS / MO_THREADS; ++u) {
+            const long long p = p0 + u * MO_THREADS;
+            v[u] = p < np ? B[p] * f[p] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < MO_PTS / MO_THREADS; ++u) asm volatile("" : "+v"(v[u]));   // read and formed here
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MO_PTS / MO_THREADS; ++u) {
+            const long long p = p0 + u * MO_THREADS;
+            if (p < np) out[p] = v[u];
+        }
+    }
+}
+
+void launch_mass_overlap(const Batch& b, const double* f, double* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(mass_overlap_kernel, dim3(1), dim3(MO_THREADS), 0, s, b, f, out);
+}
+
 // ------------------------------------------------------------------ GMRES orthogonalisation passes
 // One pass over the points of a block touches every basis vector V_0..V_J
 // once.  The body is instantiated for every basis size NJ = J+1 (J is read on

@@ -2067,15 +2067,20 @@ int sem_mass(sem_ctx* c, const double* f, double* out, int flags)
     if (!f || !out) return fail(SEM_EINVAL, "null field pointer");
     sem_ctx* one[1] = {c};
     Batch b = make_batch(one, 1);
-    VecArgs a;
-    memset(&a, 0, sizeof(a));
-    a.op = V_MASS_RAW; a.gate = -1; a.ncomp = 1; a.tv = P64; a.ta = P64; a.tb = P64; a.f0 = -1; a.f1 = -1;
-    a.x_raw = f; a.y_raw = out;
-    if ((flags & SEM_ASSEMBLE) && (f == out || !ranges_meet(f, out, 8 * (size_t)c->np))) {
+    const bool apart = f == out || !ranges_meet(f, out, 8 * (size_t)c->np);
+    if ((flags & SEM_ASSEMBLE) && apart) {
         launch_mass_dssum(b, f, out, c->stream);
         return check_hip_last();
     }
-    launch_vec(b, a, c->stream);
+    if (apart) {
+        VecArgs a;
+        memset(&a, 0, sizeof(a));
+        a.op = V_MASS_RAW; a.gate = -1; a.ncomp = 1; a.tv = P64; a.ta = P64; a.tb = P64; a.f0 = -1; a.f1 = -1;
+        a.x_raw = f; a.y_raw = out;
+        launch_vec(b, a, c->stream);
+    } else {
+        launch_mass_overlap(b, f, out, c->stream);
+    }
     if (flags & SEM_ASSEMBLE) launch_dssum(b, -1, 1, P64, -1, out, c->stream);
     return check_hip_last();
 }

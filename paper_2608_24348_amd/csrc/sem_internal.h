@@ -440,6 +440,8 @@ struct FinArgs {
 };
 
 void launch_vec(const Batch& b, const VecArgs& a, hipStream_t s);
+// out = B o f of one request, fp64 arrays that overlap at different offsets
+void launch_mass_overlap(const Batch& b, const double* f, double* out, hipStream_t s);
 void launch_fin(const Batch& b, const FinArgs& a, hipStream_t s);
 
 // Stand-alone Jacobi-GMRES Poisson solve of one bound context (any mode) on a
