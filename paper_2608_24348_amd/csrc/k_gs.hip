@@ -124,11 +124,11 @@ __device__ __forceinline__ void gs_row_task(const SEM_GLOBAL char* const* rr, SE
     U fac[GS_DEPTH + 1][MASS ? NC : 1];
     auto read = [&](int t, unsigned off) { return *(const SEM_GLOBAL U*)(rr[t] + off + (MASS ? dm.f : 0)); };
     auto read_b = [&](int t, unsigned off) { return *(const SEM_GLOBAL U*)(rr[t] + off + dm.b); };
-    auto form = [&](U (&v)[NC], const U (&b)[MASS ? NC : 1]) {
-        if constexpr (MASS) {
+    // called for MASS alone: an empty call still pins v in memory order, and two more
+    // registers cost the fifth wave of fp64 rows (12^3, N = 8: 13.2 us without, 14.6 with)
+    auto form = [&](U (&v)[NC], const U (&b)[NC]) {
 #pragma unroll
-            for (int t = 0; t < NC; ++t) v[t] = word_mul<T, V>(v[t], b[t]);
-        }
+        for (int t = 0; t < NC; ++t) v[t] = word_mul<T, V>(v[t], b[t]);
     };
     // segment s, lane (el, p); lanes past the line read its last element
     // (their values are never used)
@@ -146,7 +146,7 @@ __device__ __forceinline__ void gs_row_task(const SEM_GLOBAL char* const* rr, SE
     auto step = [&](U (&cur)[NC], U (&nxt)[NC], U (&nn)[NC], const U (&nxtb)[MASS ? NC : 1], U (&nnb)[MASS ? NC : 1],
                     int s) {
         load(nn, nnb, s + GS_DEPTH);
-        form(nxt, nxtb);
+        if constexpr (MASS) form(nxt, nxtb);
         const int ws = min(W, nx - s * W);
         const bool more = s + 1 < nseg;
         T lp[NC], rp[NC];
@@ -204,7 +204,7 @@ __device__ __forceinline__ void gs_row_task(const SEM_GLOBAL char* const* rr, SE
     }
 #pragma unroll
     for (int r = 0; r < GS_DEPTH; ++r) load(buf[r], fac[r], r);
-    form(buf[0], fac[0]);
+    if constexpr (MASS) form(buf[0], fac[0]);
     for (int s = 0;;) {
 #pragma unroll
         for (int r = 0; r <= GS_DEPTH; ++r) {
@@ -232,23 +232,22 @@ __device__ __forceinline__ void gs_put_norm(const ReqDesc* R, int pslot, int blk
 }
 
 // factors f (mf) and the request's mass matrix B, relative to the array written
-template <bool MASS> __device__ __forceinline__ GsMass gs_mass(const ReqDesc* R, const void* out, const void* mf)
+__device__ __forceinline__ GsMass gs_mass(const ReqDesc* R, const void* out, const void* mf)
 {
-    GsMass d = {0, 0};
-    if constexpr (MASS) {
-        d.f = (const char*)mf - (const char*)out;
-        d.b = (const char*)R->f[F_B64] - (const char*)out;
-    }
-    return d;
+    return {(const char*)mf - (const char*)out, (const char*)R->f[F_B64] - (const char*)out};
 }
+__device__ __forceinline__ GsMass gs_mass(const ReqDesc*, const void*) { return {0, 0}; }
 
 // Workgroup p runs task block (p % 8) * per + p / 8, so each XCD walks one
 // contiguous range; within a request the blocks go (ez, k, ey), so the two
 // blocks that share the lines of a row j = 0 are neighbours on one XCD.
-template <typename T, typename A, int V, bool MASS = false, bool MC = false>
+// MC: several components, blockIdx.y each; mf: the factor f of the mass form,
+// an argument of its instances alone.
+template <typename T, typename A, int V, bool MC, typename... MF>
 __global__ void __launch_bounds__(SEM_GS_THREADS)
-dssum_rows_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, const void* mf = nullptr)
+dssum_rows_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, MF... mf)
 {
+    constexpr bool MASS = sizeof...(MF) > 0;
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gl[bt.n]) return;
@@ -271,7 +270,7 @@ dssum_rows_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, 
     const SEM_GLOBAL T* ur = field >= 0 ? gfield<T>(R, field) : gp((const T*)raw);
     SEM_GLOBAL T* uw = field >= 0 ? gfieldw<T>(R, field) : gp((T*)raw);
     const unsigned eb = (unsigned)(L3 * sizeof(T)), ib = (unsigned)(p * V * sizeof(T));
-    const GsMass dm = gs_mass<MASS>(R, raw, mf);
+    const GsMass dm = gs_mass(R, raw, mf...);
     // the wave index is uniform; say so, so that the row bases stay scalar
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double acc = 0.0;
@@ -339,16 +338,14 @@ __device__ __forceinline__ void gs_plane_task(SEM_GLOBAL char* const* lp, unsign
         }
     };
     auto form = [&](GsSeg<U>& b, const GsSeg<U>& fb) {
-        if constexpr (MASS) {
 #pragma unroll
-            for (int z = 0; z < NZ; ++z) b.m[z] = word_mul<T, V>(b.m[z], fb.m[z]);
-        }
+        for (int z = 0; z < NZ; ++z) b.m[z] = word_mul<T, V>(b.m[z], fb.m[z]);
     };
     const bool own_y = r == 0, yb = r == 0 || r == N;
     // sum and store segment s (cur), load segment s + GS_DEPTH into nn
     auto step = [&](GsSeg<U>& cur, GsSeg<U>& nxt, GsSeg<U>& nn, const GsSeg<U>& nxtb, GsSeg<U>& nnb, int s) {
         load(nn, nnb, s + GS_DEPTH);
-        form(nxt, nxtb);
+        if constexpr (MASS) form(nxt, nxtb);
         const int ws = min(EW, nx - s * EW);
         const bool more = s + 1 < nseg;
         if (s == 0) first = cur;
@@ -434,7 +431,7 @@ __device__ __forceinline__ void gs_plane_task(SEM_GLOBAL char* const* lp, unsign
     }
 #pragma unroll
     for (int b = 0; b < GS_DEPTH; ++b) load(buf[b], fac[MASS ? b : 0], b);
-    form(buf[0], fac[0]);
+    if constexpr (MASS) form(buf[0], fac[0]);
     for (int s = 0;;) {
 #pragma unroll
         for (int b = 0; b <= GS_DEPTH; ++b) {
@@ -447,10 +444,11 @@ __device__ __forceinline__ void gs_plane_task(SEM_GLOBAL char* const* lp, unsign
 
 // Workgroup p runs task block (p % 8) * per + p / 8 (one x-line and four
 // planes k, a wave each); within a request the blocks go (ez, k / 4, ey).
-template <typename T, typename A, int V, bool MASS = false, bool MC = false>
+template <typename T, typename A, int V, bool MC, typename... MF>
 __global__ void __launch_bounds__(SEM_GS_THREADS)
-dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, const void* mf = nullptr)
+dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot, MF... mf)
 {
+    constexpr bool MASS = sizeof...(MF) > 0;
     const int pb = blockIdx.x;
     const int g = (pb & 7) * per + (pb >> 3);
     if (g >= bt.gq[bt.n]) return;
@@ -483,7 +481,7 @@ dssum_planes_kernel(Batch bt, int field, int gate, void* raw, int per, int pslot
     lp[1] = (SEM_GLOBAL char*)(u + (r == 0 ? linyz : linz) * L3 + lx * r + p * V);
     const unsigned eb = (unsigned)(L3 * sizeof(T));
     double acc = 0.0;
-    const GsMass dm = gs_mass<MASS>(R, raw, mf);
+    const GsMass dm = gs_mass(R, raw, mf...);
     if (k == N) gs_plane_task<1, V, T, A, MASS>(lp, eb, nx, EW, SL, LP, N, el, r, p, lane, pslot >= 0, acc, dm);
     else if (k < N) gs_plane_task<0, V, T, A, MASS>(lp, eb, nx, EW, SL, LP, N, el, r, p, lane, pslot >= 0, acc, dm);
     if (pslot >= 0) gs_put_norm(R, pslot, blk, acc, bt.gq[ri + 1] - bt.gq[ri]);
@@ -499,21 +497,21 @@ constexpr unsigned GS_PLANES_LDS = 32000;
 // eight XCDs, so each keeps its placement).  Three components of 5 requests of
 // 4..8^3, N = 7: 20 us in a launch each, 12 in one; of 32^3: 164 and 161.  A
 // single component keeps an instance of its own (0.2 of 5 us).
-template <typename T, typename A, int V, bool MASS>
+template <typename T, typename A, int V, typename... MF>
 static void dssum_go(const Batch& b, int field, int ncomp, int gate, void* raw, hipStream_t s, int pslot,
-                     bool planes, const void* mf)
+                     bool planes, MF... mf)
 {
     const int nblk = planes ? b.gq[b.n] : b.gl[b.n];
     const int per = (nblk + 7) / 8;
     const dim3 grid(8 * per, ncomp);
 #define DSSUM_GO(MC)                                                                                                   \
     if (planes)                                                                                                        \
-        hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MASS, MC>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b,  \
-                           field, gate, raw, per, pslot, mf);                                                          \
+        hipLaunchKernelGGL((dssum_planes_kernel<T, A, V, MC, MF...>), grid, dim3(SEM_GS_THREADS), GS_PLANES_LDS, s, b, \
+                           field, gate, raw, per, pslot, mf...);                                                       \
     else                                                                                                               \
-        hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MASS, MC>), grid, dim3(SEM_GS_THREADS), 0, s, b, field, gate,   \
-                           raw, per, pslot, mf);
-    if constexpr (!MASS) {
+        hipLaunchKernelGGL((dssum_rows_kernel<T, A, V, MC, MF...>), grid, dim3(SEM_GS_THREADS), 0, s, b, field, gate,  \
+                           raw, per, pslot, mf...);
+    if constexpr (sizeof...(MF) == 0) {
         if (ncomp > 1) {
             DSSUM_GO(true)
             return;
@@ -533,21 +531,20 @@ static void dssum_go(const Batch& b, int field, int ncomp, int gate, void* raw, 
 //   the plane fits a wave (16^3, N = 11, fp16: 13.8 us against 18.2 in rows).
 static int gs_plane_lanes(int lx, int V) { return (64 / (lx * (lx / V))) * lx * (lx / V); }
 
-template <typename T, typename A, bool MASS = false>
-static void dssum_pick(const Batch& b, int field, int ncomp, int gate, void* raw, hipStream_t s, int pslot,
-                       const void* mf = nullptr)
+template <typename T, typename A, typename... MF>
+static void dssum_pick(const Batch& b, int field, int ncomp, int gate, void* raw, hipStream_t s, int pslot, MF... mf)
 {
     const int lx = b.lx;
     constexpr int V16 = 16 / (int)sizeof(T);
     if (lx % V16 == 0) {
         const bool planes = gs_planes(lx, V16) && gs_plane_lanes(lx, V16) >= 48;
-        return dssum_go<T, A, V16, MASS>(b, field, ncomp, gate, raw, s, pslot, planes, mf);
+        return dssum_go<T, A, V16>(b, field, ncomp, gate, raw, s, pslot, planes, mf...);
     }
     if constexpr (sizeof(T) <= 2)
-        if (lx % 4 == 0) return dssum_go<T, A, 4, MASS>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 4), mf);
+        if (lx % 4 == 0) return dssum_go<T, A, 4>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 4), mf...);
     if constexpr (sizeof(T) <= 4)
-        if (lx % 2 == 0) return dssum_go<T, A, 2, MASS>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 2), mf);
-    dssum_go<T, A, 1, MASS>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 1), mf);
+        if (lx % 2 == 0) return dssum_go<T, A, 2>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 2), mf...);
+    dssum_go<T, A, 1>(b, field, ncomp, gate, raw, s, pslot, gs_planes(lx, 1), mf...);
 }
 
 void launch_dssum(const Batch& b, int field, int ncomp, int tprec, int gate, void* raw, hipStream_t s, int pslot)
@@ -567,7 +564,7 @@ void launch_dssum(const Batch& b, int field, int ncomp, int tprec, int gate, voi
 void launch_mass_dssum(const Batch& b, const double* f, double* out, hipStream_t s)
 {
     if (b.gl[b.n] == 0) return;
-    dssum_pick<double, double, true>(b, -1, 1, -1, out, s, -1, f);
+    dssum_pick<double, double>(b, -1, 1, -1, out, s, -1, f);
 }
 
 }  // namespace semk
