@@ -423,16 +423,21 @@ __global__ void __launch_bounds__((epb_of(LX) * LX * LX + 63) / 64 * 64) axw_dot
 
 // Without the fused dot a wave is a workgroup of its own.  With it the
 // workgroups are the element blocks its partial sums are defined on, except
-// where these hold more than two waves and fill the chip: then the waves still
-// run alone and leave their column dots in the scratch field a.dots.  (At lx =
-// 10 a CU holds one workgroup of five fp64 waves, where eight fit: 20^3, three
-// components, 407 us against 330 with single waves.)
+// where these hold more than two waves and do not run in one round: then the
+// waves still run alone and leave their column dots in the scratch field a.dots.
+// At lx = 10 a CU holds three blocks of five fp32 waves or one of fp64, where 16
+// and eight waves fit.  Three components and their dots, us, blocks against single
+// waves: 1440 elements (864 blocks) fp32 49.5 / 38.0, fp64 84.7 / 67.9 (column
+// kernel 46.4, 96.5).  Up to 768 blocks the three of a CU run in one round (1280
+// elements, fp32: blocks 35.5, column kernel 37.2).
 template <int LX, typename TU, typename TG, typename C, int H16 = 0>
 static void axw_go(const Batch& b, const AxLaunch& a0, hipStream_t s)
 {
     constexpr int EPB = epb_of(LX);
+    // 16-bit arithmetic at lx = 10 comes here neither scaled nor with the dot (ax_wide)
+    constexpr bool ALONE = LX == 10 && H16 != 0;
     AxLaunch a = a0;
-    if (a.pdot >= 0 && (EPB <= 2 || b.el[b.n] < 2048)) a.dots = -1;
+    if (a.pdot >= 0 && (EPB <= 2 || b.eb[b.n] * a.ncomp <= 768)) a.dots = -1;
     const bool blocks = a.pdot >= 0 && a.dots < 0;
     const int n = blocks ? b.eb[b.n] : b.el[b.n];
     const dim3 grid(((n + 7) / 8) * 8 * a.ncomp);
@@ -440,9 +445,11 @@ static void axw_go(const Batch& b, const AxLaunch& a0, hipStream_t s)
     if constexpr (sizeof(TU) == 4) {
         // the Arnoldi operator of an fp32 GMRES basis
         if (a.out64) {
-            if (a.precond >= 0 && a.tpc == P64) AXW_GO(1, 1, double, 0, H16);
-            else if (a.precond >= 0) AXW_GO(1, 2, double, 0, H16);
-            else AXW_GO(1, 0, double, 0, H16);
+            if constexpr (!ALONE) {
+                if (a.precond >= 0 && a.tpc == P64) { AXW_GO(1, 1, double, 0, H16); return; }
+                if (a.precond >= 0) { AXW_GO(1, 2, double, 0, H16); return; }
+            }
+            AXW_GO(1, 0, double, 0, H16);
             return;
         }
     }
@@ -458,10 +465,12 @@ static void axw_go(const Batch& b, const AxLaunch& a0, hipStream_t s)
             return;
         }
     }
-    if (blocks) {
-        if (a.ncomp > 1) AXW_GO(EPB, 0, TU, 0, H16, 1);
-        else AXW_GO(EPB, 0, TU, 0, H16);
-        return;
+    if constexpr (!ALONE) {
+        if (blocks) {
+            if (a.ncomp > 1) AXW_GO(EPB, 0, TU, 0, H16, 1);
+            else AXW_GO(EPB, 0, TU, 0, H16);
+            return;
+        }
     }
     if (a.ncomp > 1) AXW_GO(1, 0, TU, 0, H16, 1);
     else AXW_GO(1, 0, TU, 0, H16);

@@ -4,6 +4,9 @@ computes the same alone (column kernel) and in a batch that fills the chip;
 against the oracle the large launches meet the bounds of the small ones (with
 stored fp32 or 16-bit geometry, whose rounding the bounds are made of; fp64
 geometry is covered by the bitwise comparison)."""
+# At N = 9 fp64 arithmetic has no column form: there both sides of the comparison
+# run on matrix cores.  The one-component pressure operators of these batches stay
+# with the column kernel.  test_gpu_wide_rule.py takes both, and the Jacobi forms.
 import numpy as np
 import pytest
 
