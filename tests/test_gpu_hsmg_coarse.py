@@ -40,3 +40,25 @@ def test_coarse_solve_forms_agree(q, tier):
         assert torch.equal(a, b)
     small.close()
     large.close()
+
+
+@pytest.mark.parametrize("nel", LARGE)
+def test_three_launch_coarse_solve_matches_oracle(nel):
+    """The larger grids alone (equal cubic elements): iteration counts of the
+    oracle's multigrid solve and its solution within 1e-8, the bars of the other
+    multigrid solves at the same tolerance."""
+    import numpy as np
+    from oracle import OracleHSMG
+    from paper_2608_24348_amd import inputs
+    half = [np.pi / 32 * n for n in nel]
+    lo, hi = [-h for h in half], half
+    m = OracleMesh(nel, 4, lo=lo, hi=hi)
+    rhs = m.dssum(m.mass() * m.from_lattice(inputs.lattice_normal(nel, 4, 6)))
+    ref, it, _ = OracleHSMG(m).poisson(rhs, tol=1e-10, maxit=2000)
+    c = sem.Context(sem.mesh_desc(nel, 4, lo=lo, hi=hi), sem.flow_desc(mode=sem.MODE_POISSON, hsmg=1, pres_tol=1e-10, pres_maxit=2000),
+                    sem.tier("fp64"), device="cuda:0")
+    sol = torch.empty(c.np, dtype=torch.float64, device="cuda:0")
+    st = sem.poisson_solve([c], [torch.from_numpy(rhs).to("cuda:0")], [sol])[0]
+    assert st["status"] == 0 and st["iters"] == it, (st, it)
+    assert np.abs(sol.cpu().numpy() - ref).max() < 1e-8 * np.abs(ref).max()
+    c.close()
