@@ -223,25 +223,39 @@ PROF_KERNELS = {
 }
 
 
-KERNEL_SOURCES = {"ax_resid": ("k_ax.h", "k_ax.hip", "k_ax8.hip", "k_common.h", "sem_internal.h"),
-                  "ax_presid": ("k_ax.h", "k_ax.hip", "k_ax8.hip", "k_common.h", "sem_internal.h"),
-                  "ax_vel": ("k_ax.h", "k_ax.hip", "k_ax8.hip", "k_common.h", "sem_internal.h"),
-                  "ax_pres": ("k_ax.h", "k_ax.hip", "k_ax8.hip", "k_common.h", "sem_internal.h")}
+def ax_kernel(N, form="..."):
+    """Kernel of a Helmholtz operator launch.  From N = 9 on the library takes
+    the column or the matrix-core kernel by the launch's size and type (ax_wide
+    in k_ax.hip); N = 9 in fp64 arithmetic has the matrix-core kernel alone."""
+    column, wide = "ax_kernel<%d, %s>" % (N + 1, form), "axw_kernel<%d, ...>" % (N + 1)
+    if N < 9:
+        return column
+    return wide if N == 9 and form.startswith("double, double, double") else "%s or %s, by launch size" % (wide, column)
 
 
-def kernel_sources_sha(kind="gm_upd_dots"):
+def kernel_sources(kind, N=7):
+    """Sources that make a kernel class at order N."""
+    if kind not in ("ax_resid", "ax_presid", "ax_vel", "ax_pres"):
+        return ("k_vec.hip", "k_common.h", "k_fin.h", "sem_internal.h")
+    own = ((("k_ax8.hip",) if N in (7, 8) else ()) if N < 9 else
+           ("k_axw.h", "k_axw%d.hip" % (N + 1), "k_ax12.hip" if N == 11 else "k_ax10.hip"))
+    mfma = ("k_axm.hip",) if N == 7 and kind in ("ax_vel", "ax_pres") else ()   # 16-bit geometry
+    return ("k_ax.h", "k_ax.hip") + own + mfma + ("k_common.h", "sem_internal.h")
+
+
+def kernel_sources_sha(kind="gm_upd_dots", N=7):
     """Hash of the sources that make a kernel class (a stored PMC traffic
     figure is valid only for the exact kernel it was taken on)."""
     import hashlib
     h = hashlib.sha256()
     base = os.path.join(ROOT, "paper_2608_24348_amd", "csrc")
-    for f in KERNEL_SOURCES.get(kind, ("k_vec.hip", "k_common.h", "k_fin.h", "sem_internal.h")):
+    for f in kernel_sources(kind, N):
         with open(os.path.join(base, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
 
-def stored_traffic(kind, tier, workload):
+def stored_traffic(kind, tier, workload, N=7):
     """HBM bytes per launch from the committed rocprofv3 PMC summary of this
     kernel class and workload, if it was taken on the current kernel sources."""
     path = os.path.join(ROOT, "profiles", "pmc_%s_%s.json" % (kind, tier))
@@ -249,7 +263,7 @@ def stored_traffic(kind, tier, workload):
         return None
     with open(path) as fh:
         d = json.load(fh)
-    if d.get("sources_sha256") != kernel_sources_sha(kind) or d.get("workload") != workload:
+    if d.get("sources_sha256") != kernel_sources_sha(kind, N) or d.get("workload") != workload:
         return None
     return d["hbm_bytes_per_launch"]
 
@@ -296,7 +310,7 @@ def roofline(kind, tier, prof, steps, npts, workload, N=7, dealias=0):
             nv = 1 + (s["vcyc"] if tier != "fp64" else 0)
             alg += nv * npts * 128
             active += nv
-        name = "ax_kernel<%d, double, double, double, 0, double, 1, 0, 1> -- fp64 velocity residual RHS_L - H_L u" % (N + 1)
+        name = ax_kernel(N, "double, double, double, 0, double, 1, 0, 1") + " -- fp64 velocity residual RHS_L - H_L u"
     elif kind == "ax_presid":
         # fp64 Poisson residual operator at the end of every GMRES cycle that
         # started from a nonzero iterate (u, w, 6 G = 64 B/point); the other
@@ -307,7 +321,7 @@ def roofline(kind, tier, prof, steps, npts, workload, N=7, dealias=0):
             ncyc = (s["pit"] + 29) // 30 if s["pit"] > 0 else 0
             alg += ncyc * npts * 64
             active += ncyc
-        name = "ax_kernel<%d, double, double, double, 0, double, 0, 0, 0> -- fp64 GMRES cycle-end residual" % (N + 1)
+        name = ax_kernel(N, "double, double, double, 0, double, 0, 0, 0") + " -- fp64 GMRES cycle-end residual"
     elif kind in PROF_KERNELS:
         kname, what, fbytes = PROF_KERNELS[kind]
         alg = 0.0
@@ -336,13 +350,13 @@ def roofline(kind, tier, prof, steps, npts, workload, N=7, dealias=0):
     elif kind == "ax_vel":
         active = sum(sum(s["vit"]) for s in steps)  # component launches that did work
         alg = active * npts * _bytes_per_point(kind, tier)
-        name = "ax_kernel<%d,...> velocity Helmholtz operator (PCG)" % (N + 1)
+        name = ax_kernel(N) + " velocity Helmholtz operator (PCG)"
     else:
         active = sum(s["pit"] for s in steps)
         alg = active * npts * _bytes_per_point(kind, tier)
-        name = "ax_kernel<%d,...> pressure operator (Arnoldi step)" % (N + 1)
+        name = ax_kernel(N) + " pressure operator (Arnoldi step)"
     achieved = alg / (tot_ms * 1e-3) / 1e9 if tot_ms > 0 else 0.0
-    traffic = stored_traffic(kind, tier, workload)
+    traffic = stored_traffic(kind, tier, workload, N)
     return {"kernel": name, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "launches": nlaunch, "active_units": active,
             "kernel_ms_total": tot_ms, "avg_launch_ms": tot_ms / max(nlaunch, 1),

@@ -54,3 +54,18 @@ def test_stored_traffic_needs_the_same_kernel_sources_and_workload():
 
 def test_gmres_index_sequence_restarts_every_m():
     assert bench.gmres_j_sequence(7, 3) == [0, 1, 2, 0, 1, 2, 0]
+
+
+@pytest.mark.parametrize("kind", ["ax_resid", "ax_presid", "ax_vel", "ax_pres"])
+def test_operator_kernel_and_sources_follow_the_order(kind):
+    base = os.path.join(ROOT, "paper_2608_24348_amd", "csrc")
+    for N in range(2, 12):
+        src = bench.kernel_sources(kind, N)
+        assert all(os.path.exists(os.path.join(base, f)) for f in src)
+        # the source that holds the order's column launcher, and from N = 9 on the matrix-core one
+        text = "".join(open(os.path.join(base, f)).read() for f in src)
+        assert ("launch_ax_col%d(const Batch& b" % (N + 1) if N > 6 else "ax_lx<%d>(b, a, s)" % (N + 1)) in text
+        assert ("launch_ax_wide%d(const Batch& b" % (N + 1) in text) == (N > 8)
+        name = bench.roofline(kind, "fp64", (1.0, 1), _steps(1), (N + 1) ** 3, "w", N=N)["kernel"]
+        assert ("axw_kernel<%d" % (N + 1) in name) == (N > 8)
+    assert bench.kernel_sources_sha(kind, 7) != bench.kernel_sources_sha(kind, 11)
