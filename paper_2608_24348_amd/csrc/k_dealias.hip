@@ -210,20 +210,25 @@ template <typename TM, typename C> __device__ __forceinline__ C mscale(const Req
 // multiply-adds; T adds its terms in the order K0, K1, K2.
 //
 // Bound by memory at LX <= 7 (the metric terms: 9 of 15 words at 3.4 times the
-// points) and by latency and the coefficients above: at LX = 12, fp64, without
-// coefficient reads 717, without metric loads 942, with neither nor u nor stores
-// 348 of 1233 us, VALU busy 24%, against 396 us for the bytes.  A tile form on
-// matrix cores pads lines of LX and LXD to 4 and 16, and passes V and T of a
-// component through LDS; lines pad only the last of their waves.  us a call,
-// tile form (LX <= 10) or one thread a point (11, 12) before, lines now:
+// points), above by waiting: in fp64 one workgroup of four (LX = 10) or six (12)
+// waves a CU.  Counters there, LX = 10 and 12: VALU busy 24 and 32%, LDS 12 and 18%
+// of the cycles (27 and 16% of that in conflicts), waves waiting 49 and 62% of
+// theirs; 2.06 GB read from memory at LX = 12 where 1.89 are needed (977 us, 396 for
+// the bytes).  A tile form on matrix cores pads lines of LX and LXD to 4 and 16, and
+// passes V and T of a component through LDS; lines pad only the last of their waves.
+// us a call, tile form (LX <= 10) or one thread a point (11, 12) before, lines now:
 //   LX, elements     fp64          fp32          16-bit terms
+//    3, 40^3         439 -> 245    358 -> 133    369 -> 147
+//    4, 32^3         327 -> 162    245 -> 95     252 -> 106
 //    5, 32^3         665 -> 303    363 -> 186    377 -> 145
+//    6, 24^3         443 -> 222    251 -> 150    274 -> 133
 //    7, 32 32 16     783 -> 459    390 -> 254    392 -> 234
 //    8, 32^3        1718 -> 1656   829 -> 742    782 -> 722
 //    9, 22^3        2396 -> 785    586 -> 415    535 -> 415
 //   10, 20^3        2302 -> 1125   577 -> 443    515 -> 420
 //   11, 18^3        3161 -> 1131  1954 -> 818   1960 -> 817
 //   12, 16^3        2388 -> 977   1298 -> 697   1291 -> 678
+// and with few elements, 2^3: LX = 3 45 -> 11, 8 48 -> 25, 12 275 -> 51 in fp64.
 template <int LX, typename C> struct Dn {
     static constexpr int LXD = (3 * LX + 1) / 2, NL = LX * LX, NN = LXD * LXD, N3 = NL * LX, ND3 = NN * LXD;
     static constexpr int LJ = LX | 1, LP = LXD | 1;   // odd row strides: lanes a row apart fall in different banks

@@ -362,6 +362,14 @@ void launch_mass_overlap(const Batch& b, const double* f, double* out, hipStream
 }
 
 // ------------------------------------------------------------------ GMRES orthogonalisation passes
+// a value that every lane holds, in scalar registers (the coefficients of a pass took 62 vector registers)
+__device__ __forceinline__ double scalar(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // One pass over the points of a block touches every basis vector V_0..V_J
 // once.  The body is instantiated for every basis size NJ = J+1 (J is read on
 // the device and dispatched with a uniform switch), so each point issues its
@@ -371,14 +379,6 @@ void launch_mass_overlap(const Batch& b, const double* f, double* out, hipStream
 // over unique nodes and the second subtracts that mean: a no-op in exact
 // arithmetic that keeps rounding (notably of fp32 operators) from feeding the
 // null direction into the basis.
-// a value that every lane holds, in scalar registers (the coefficients of a pass took 62 vector registers)
-__device__ __forceinline__ double scalar(double v)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
-}
-
 template <int NJ, int MODE, typename TB>
 __device__ __forceinline__ void gm_body(const ReqDesc* R, const PtRange& pr, double* acc, double& accm)
 {
