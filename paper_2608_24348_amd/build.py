@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsem.so")
-SOURCES = ["k_ops.hip", "k_ax10.hip", "k_ax.hip", "k_ax8.hip", "k_ax12.hip", "k_axw12.hip", "k_axw10.hip", "k_axw11.hip",
+SOURCES = ["k_ax10.hip", "k_ax.hip", "k_ax8.hip", "k_ax12.hip", "k_axw12.hip", "k_axw10.hip", "k_axw11.hip", "k_ops.hip",
            "k_axm.hip", "k_gs.hip", "k_geom.hip", "k_dealias.hip", "k_vec.hip", "k_hsmg.hip", "sem_host.cpp", "sem_noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

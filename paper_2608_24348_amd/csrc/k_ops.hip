@@ -67,37 +67,36 @@ __device__ __forceinline__ void load_D(const ReqDesc* R, C* sD)
     }
 }
 
-// Component c of an operator's input or output: the request's field id + c, or
-// the caller's array where a standalone call passes its OpArrays.  The two are
-// instances of their own: chosen at run time, the output pointers stay in
-// registers through the k-walk (fp64 conv, 12^3, N = 8: 72.6 us, 64.8 without;
-// opgrad, 12 12 10, N = 10: 51.6 and 46.0).
-template <typename... IO>
-__device__ __forceinline__ const SEM_GLOBAL double* op_src(const ReqDesc* R, int id, int c, const IO&... io)
+// An address that every lane holds, in scalar registers.  Output addresses read
+// from the request's table ahead of the k-walk come as vector values and stay in
+// six registers through it; read at each store they are loaded again and again.
+// us in a step, in vector registers / at each store / scalar: conv fp64 20^3, N = 7
+// 117 / 107 / 100, 12^3, N = 11 177 / 167 / 165; wdiv fp64 20^3, N = 7 80 / 90 / 80
+// (inputs).
+template <typename T> __device__ __forceinline__ SEM_GLOBAL T* uniform(SEM_GLOBAL T* p)
 {
-    if constexpr (sizeof...(IO) > 0) return gp((io.in[c], ...));
-    else return gfield<double>(R, id + c);
-}
-template <typename... IO>
-__device__ __forceinline__ SEM_GLOBAL double* op_dst(const ReqDesc* R, int id, int c, const IO&... io)
-{
-    if constexpr (sizeof...(IO) > 0) return gp((io.out[c], ...));
-    else return gfieldw<double>(R, id + c);
+    const uintptr_t a = (uintptr_t)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (SEM_GLOBAL T*)(((uintptr_t)hi << 32) | lo);
 }
 
-template <int LX, typename TM, typename C, typename... IO>
-__global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, IO... io)
+template <int LX, typename TM, typename C>
+__global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, OpArrays io)
 {
     OPS_PROLOGUE(LX)
+    // (fp32 sums at LX = 12 schedule worse so: 12^3 elements 108 us in vector registers, 117)
+    constexpr bool VOUT = LX == 12 && sizeof(C) == 4;
     __shared__ C sD[L2];
     __shared__ C su[3][EPB][L2];
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
+    SEM_GLOBAL double* out[3];
+    for (int f = 0; f < 3; ++f) out[f] = VOUT ? op_out(R, io, F_BN, f) : uniform(op_out(R, io, F_BN, f));
     C col[3][LX];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const SEM_GLOBAL double* u = op_src(R, F_U, c, io...);
+        const SEM_GLOBAL double* u = op_in(R, io, F_U, c);
 #pragma unroll
         for (int k = 0; k < LX; ++k) col[c][k] = (C)u[ebase + k * L2 + ij];
     }
@@ -126,7 +125,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, IO... io)
                 C s = 0;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) s += col[c][k] * (m[0 * 3 + c] * dr + m[1 * 3 + c] * ds + m[2 * 3 + c] * dt);
-                op_dst(R, F_BN, f, io...)[ebase + p] = -(double)s;
+                out[f][ebase + p] = -(double)s;
             }
         }
         lds_handoff<OWave<LX>::v>();
@@ -137,8 +136,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) conv_kernel(Batch bt, IO... io)
 // velocity rhs of the BDF/EXT step point by point,
 //   rhs_c = sum_q a_q BN_c^{n-q} + (B / dt) sum_q b_q u_c^{n-q} - (grad p)_c,
 // so grad p is never written and read back (48 bytes per point)
-template <int LX, typename TM, typename C, bool RHS, typename... IO>
-__global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src, int dst, IO... io)
+template <int LX, typename TM, typename C, bool RHS = false>
+__global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src, int dst, OpArrays io)
 {
     OPS_PROLOGUE(LX)
     __shared__ C sD[L2];
@@ -146,7 +145,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
-    const SEM_GLOBAL double* u = op_src(R, src, 0, io...);
+    const SEM_GLOBAL double* u = op_in(R, io, src, 0);
     double a1 = 0, a2 = 0, a3 = 0, b1 = 0, b2 = 0, b3 = 0, idt = 0;
     if constexpr (RHS) {
         const SEM_GLOBAL double* S = gp(R->S);
@@ -154,6 +153,11 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
         b1 = S[S_BDF]; b2 = S[S_BDF + 1]; b3 = S[S_BDF + 2];
         idt = 1.0 / S[S_DT];
     }
+    SEM_GLOBAL double* out[3];
+    // (fp64 at LX = 12 at each store: 192 elements 34.6 us against 37.7 scalar; 12^3 66 and 63, vector 80)
+    constexpr bool LATE = LX == 12 && sizeof(C) == 8 && !RHS;
+    if constexpr (!LATE)
+        for (int c = 0; c < 3; ++c) out[c] = uniform(RHS ? gfieldw<double>(R, F_RHS + c) : op_out(R, io, dst, c));
     C col[LX];
 #pragma unroll
     for (int k = 0; k < LX; ++k) col[k] = (C)u[ebase + k * L2 + ij];
@@ -188,16 +192,17 @@ __global__ void __launch_bounds__(ONthr<LX>::v) opgrad_kernel(Batch bt, int src,
                 C gc = ldm<TM, C>(M, ((long long)ee * 9 + 0 * 3 + c) * L3 + p, msc) * dr
                      + ldm<TM, C>(M, ((long long)ee * 9 + 1 * 3 + c) * L3 + p, msc) * ds
                      + ldm<TM, C>(M, ((long long)ee * 9 + 2 * 3 + c) * L3 + p, msc) * dt;
-                if constexpr (RHS) gfieldw<double>(R, F_RHS + c)[ebase + p] = ev[c] + (bv * idt) * hv[c] - (double)gc;
-                else op_dst(R, dst, c, io...)[ebase + p] = (double)gc;
+                if constexpr (RHS) out[c][ebase + p] = ev[c] + (bv * idt) * hv[c] - (double)gc;
+                else if constexpr (LATE) op_out(R, io, dst, c)[ebase + p] = (double)gc;
+                else out[c][ebase + p] = (double)gc;
             }
         }
         lds_handoff<OWave<LX>::v>();
     }
 }
 
-template <int LX, typename TM, typename C, typename... IO>
-__global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, int dst, IO... io)
+template <int LX, typename TM, typename C>
+__global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, int dst, OpArrays io)
 {
     OPS_PROLOGUE(LX)
     __shared__ C sD[L2];
@@ -206,6 +211,8 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
     load_D<LX, C>(R, sD);
     const SEM_GLOBAL TM* M = gfield<TM>(R, mfield<TM>());
     const C msc = melem_scale<TM, C>(R, ee);
+    const SEM_GLOBAL double* in[3];
+    for (int c = 0; c < 3; ++c) in[c] = uniform(op_in(R, io, src, c));
     C wacc[LX];
 #pragma unroll
     for (int k = 0; k < LX; ++k) wacc[k] = 0;
@@ -217,7 +224,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
         if (live) {
             C v[3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[c] = (C)op_src(R, src, c, io...)[ebase + p];
+            for (int c = 0; c < 3; ++c) v[c] = (C)in[c][ebase + p];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -239,7 +246,7 @@ __global__ void __launch_bounds__(ONthr<LX>::v) wdiv_kernel(Batch bt, int src, i
         lds_handoff<OWave<LX>::v>();
     }
     if (live) {
-        SEM_GLOBAL double* out = op_dst(R, dst, 0, io...);
+        SEM_GLOBAL double* out = op_out(R, io, dst, 0);
 #pragma unroll
         for (int k = 0; k < LX; ++k) out[ebase + k * L2 + ij] = (double)wacc[k];
     }
@@ -353,69 +360,54 @@ __global__ void __launch_bounds__(ONthr<LX>::v) diagnostics_kernel(Batch bt)
     case 11: CALL(11); break; case 12: CALL(12); break; default: break; }
 
 // supported (metric storage, arithmetic) pairs: (fp64, fp64), (fp32, fp32),
-// (fp16, fp32), (bf16, fp32) and (fp32, fp64); TAIL: the kernel's further
-// template arguments
-#define OPS_DISPATCH(KERNEL, TAIL, L, grid, blk, s, ...)                                                                   \
-    if (tm == P64) hipLaunchKernelGGL((KERNEL<L, double, double TAIL>), grid, blk, 0, s, __VA_ARGS__);                \
-    else if (tm == P32 && tc == P64) hipLaunchKernelGGL((KERNEL<L, float, double TAIL>), grid, blk, 0, s, __VA_ARGS__); \
-    else if (tm == P32) hipLaunchKernelGGL((KERNEL<L, float, float TAIL>), grid, blk, 0, s, __VA_ARGS__);             \
-    else if (tm == P16) hipLaunchKernelGGL((KERNEL<L, __half, float TAIL>), grid, blk, 0, s, __VA_ARGS__);            \
-    else hipLaunchKernelGGL((KERNEL<L, __hip_bfloat16, float TAIL>), grid, blk, 0, s, __VA_ARGS__);
-#define OPS_IO , IO...
-#define OPS_GRAD , false, IO...
-#define OPS_RHS , true
-
-template <typename... IO>
-static void conv_go(const Batch& b, int lx, int tm, int tc, hipStream_t s, const IO&... io)
-{
-    dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(conv_kernel, OPS_IO, L, grid, dim3(ONthr<L>::v), s, b, io...)
-    OPS_LX_SWITCH(lx, GO)
-#undef GO
-}
+// (fp16, fp32), (bf16, fp32) and (fp32, fp64)
+#define OPS_DISPATCH(KERNEL, L, grid, blk, s, ...)                                                                  \
+    if (tm == P64) hipLaunchKernelGGL((KERNEL<L, double, double>), grid, blk, 0, s, __VA_ARGS__);                 \
+    else if (tm == P32 && tc == P64) hipLaunchKernelGGL((KERNEL<L, float, double>), grid, blk, 0, s, __VA_ARGS__);\
+    else if (tm == P32) hipLaunchKernelGGL((KERNEL<L, float, float>), grid, blk, 0, s, __VA_ARGS__);              \
+    else if (tm == P16) hipLaunchKernelGGL((KERNEL<L, __half, float>), grid, blk, 0, s, __VA_ARGS__);             \
+    else hipLaunchKernelGGL((KERNEL<L, __hip_bfloat16, float>), grid, blk, 0, s, __VA_ARGS__);
 
 void launch_conv(const Batch& b, int lx, int tm, int tc, hipStream_t s, const OpArrays* arrays)
 {
-    if (arrays) conv_go(b, lx, tm, tc, s, *arrays);
-    else conv_go(b, lx, tm, tc, s);
-}
-
-template <typename... IO>
-static void opgrad_go(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const IO&... io)
-{
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(opgrad_kernel, OPS_GRAD, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io...)
+#define GO(L) OPS_DISPATCH(conv_kernel, L, grid, dim3(ONthr<L>::v), s, b, io)
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
 void launch_opgrad(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const OpArrays* arrays)
 {
-    if (arrays) opgrad_go(b, lx, tm, tc, src, dst, s, *arrays);
-    else opgrad_go(b, lx, tm, tc, src, dst, s);
-}
-
-void launch_opgrad_rhs(const Batch& b, int lx, int tm, int tc, int src, hipStream_t s)
-{
+    const OpArrays io = arrays ? *arrays : OpArrays{};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(opgrad_kernel, OPS_RHS, L, grid, dim3(ONthr<L>::v), s, b, src, -1)
+#define GO(L) OPS_DISPATCH(opgrad_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io)
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
-template <typename... IO>
-static void wdiv_go(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const IO&... io)
+void launch_opgrad_rhs(const Batch& b, int lx, int tm, int tc, int src, hipStream_t s)
 {
+    const OpArrays io = {};
     dim3 grid(b.eb[b.n]);
-#define GO(L) OPS_DISPATCH(wdiv_kernel, OPS_IO, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io...)
+#define GO(L)                                                                                                          \
+    if (tm == P64) hipLaunchKernelGGL((opgrad_kernel<L, double, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
+    else if (tm == P32 && tc == P64)                                                                                   \
+        hipLaunchKernelGGL((opgrad_kernel<L, float, double, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io);       \
+    else if (tm == P32) hipLaunchKernelGGL((opgrad_kernel<L, float, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
+    else if (tm == P16) hipLaunchKernelGGL((opgrad_kernel<L, __half, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io); \
+    else hipLaunchKernelGGL((opgrad_kernel<L, __hip_bfloat16, float, true>), grid, dim3(ONthr<L>::v), 0, s, b, src, -1, io);
     OPS_LX_SWITCH(lx, GO)
 #undef GO
 }
 
 void launch_wdiv(const Batch& b, int lx, int tm, int tc, int src, int dst, hipStream_t s, const OpArrays* arrays)
 {
-    if (arrays) wdiv_go(b, lx, tm, tc, src, dst, s, *arrays);
-    else wdiv_go(b, lx, tm, tc, src, dst, s);
+    const OpArrays io = arrays ? *arrays : OpArrays{};
+    dim3 grid(b.eb[b.n]);
+#define GO(L) OPS_DISPATCH(wdiv_kernel, L, grid, dim3(ONthr<L>::v), s, b, src, dst, io)
+    OPS_LX_SWITCH(lx, GO)
+#undef GO
 }
 
 void launch_diagnostics(const Batch& b, int lx, hipStream_t s)
