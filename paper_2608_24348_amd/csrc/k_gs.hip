@@ -124,8 +124,9 @@ __device__ __forceinline__ void gs_row_task(const SEM_GLOBAL char* const* rr, SE
     U fac[GS_DEPTH + 1][MASS ? NC : 1];
     auto read = [&](int t, unsigned off) { return *(const SEM_GLOBAL U*)(rr[t] + off + (MASS ? dm.f : 0)); };
     auto read_b = [&](int t, unsigned off) { return *(const SEM_GLOBAL U*)(rr[t] + off + dm.b); };
-    // called for MASS alone: an empty call still pins v in memory order, and two more
-    // registers cost the fifth wave of fp64 rows (12^3, N = 8: 13.2 us without, 14.6 with)
+    // called for MASS alone: with an empty call in them the plain kernels hold two more
+    // registers, which cost fp64 rows the fifth wave a SIMD (12 12 10, N = 10: 13.2 us
+    // without the call, 14.6 with it)
     auto form = [&](U (&v)[NC], const U (&b)[NC]) {
 #pragma unroll
         for (int t = 0; t < NC; ++t) v[t] = word_mul<T, V>(v[t], b[t]);
